@@ -401,12 +401,10 @@ typedef struct {
                                 (NULL: from X row r) */
   int32_t *work_queues;      /* device, 16 int32 zero on entry and left zero, as in mz_q4_gemm_queued
                                 (NULL: one workgroup per tile); epilogues 0-2 only */
-  void *workspace;           /* device scratch, not shared with launches in flight: the rows after the
-                                last whole 256-row tile run split over K in it (as mz_q4_gemm_split)
-                                when their tiles alone would leave most compute units idle (NULL:
-                                they run as 64-row tiles); and a product with too few 256-row tiles
-                                for the GPU but a long K range runs in it as 256-row tiles split over
-                                K (mz_q4_gemm_long_k_splits; NULL: as 64-row tiles over all of K) */
+  void *workspace;           /* device scratch, not shared with launches in flight: a product, or its
+                                rows after the last whole 256-row tile, runs split over K in it (as
+                                mz_q4_gemm_split) where its tiles over the whole K range would leave
+                                most compute units idle (NULL: over all of K) */
   int64_t workspace_bytes;
   /* rotary epilogues (Sec. 2.1 prefill, rotate-half pairs i, i + head_dim/2 of every head) */
   const int32_t *pos;        /* device int32 [m]: position of output row r */
@@ -455,10 +453,11 @@ mz_status mz_q4_gemv(const void *x_f16, int32_t k, const void *w_packed, int32_t
                      const mz_q4_gemm_args *args, const float *h_norm, float eps, void *y, void *stream);
 
 /* Split-K form of mz_q4_gemm for few rows (the short requests of the
- * paper's evaluation, Sec. 6, and every decode step): a grid of 256-column
+ * paper's evaluation, Sec. 6, and every decode step): a grid of output
  * tiles alone leaves most of the GPU idle there.  The k / 64 steps are cut
- * into n_split ranges of ceil((k / 64) / n_split) steps; each range runs as
- * its own workgroups and leaves its fp32 sums in workspace; a second kernel
+ * into at most n_split equal ranges (fewer, or one, where that is faster;
+ * always the same for the same arguments); each range runs as its own
+ * workgroups and leaves its fp32 sums in workspace; a second kernel
  * adds the ranges in order and applies the epilogue, so results are
  * deterministic and equal mz_q4_gemm's up to the order of the fp32 sums.
  * workspace: device, caller-owned, at least
@@ -493,18 +492,18 @@ mz_status mz_q4_gemm_split_noalloc(const void *x_f16, int32_t m, int32_t n_pad, 
                                    const void *w_packed, int32_t epilogue, void *y, int32_t n_split,
                                    void *stream);
 
-/* The split count the restore uses for this shape with workspace_bytes of
- * workspace: about two workgroups per compute unit, at least 4 K steps per
+/* A split count for mz_q4_gemm_split with workspace_bytes of workspace: enough
+ * for two workgroups of 64-row tiles per compute unit, at least 4 K steps per
  * split, at most 32 splits; 1 when the tile grid already fills the GPU, or
- * when m >= 1024 and the tiles cover half of its compute units. */
+ * when m >= 1024 and the tiles cover half of its compute units.  Of these the
+ * call takes the number that is fastest. */
 int32_t mz_q4_gemm_auto_splits(int32_t m, int32_t n_pad, int32_t k, int64_t workspace_bytes);
 
-/* The K splits mz_q4_gemm_ex takes with workspace_bytes of workspace when
- * the product's 256-row tiles alone are too few for the GPU while its 64-row
- * tiles fill it: 256-row tiles split into about one round of the compute
- * units, when every split keeps at least 16 K steps of 64 and the fp32
- * partials (splits x m x n_pad x 4 bytes) fit the workspace; 1 otherwise
- * (64-row tiles over the whole K range).  Host only, no GPU work. */
+/* The K splits with which a product whose 256-row tiles are too few for the
+ * GPU, while its 64-row tiles would fill it, makes about one round of the
+ * compute units of 256-row tiles, when every split keeps at least 16 K steps
+ * of 64 and the fp32 partials (splits x m x n_pad x 4 bytes) fit
+ * workspace_bytes; 1 otherwise.  Host only, no GPU work. */
 int32_t mz_q4_gemm_long_k_splits(int32_t m, int32_t n_pad, int32_t k, int64_t workspace_bytes);
 
 /* Causal GQA attention (paper Sec. 2.1; read through the chunk table as in

@@ -1,6 +1,9 @@
 // Q4_0-weight GEMM for gfx950: Y = X . W^T, X f16 [m][k], W Q4_0 [n][k]; optionally
 // Y[r] = X[a_rows[r]] . W^T (the rows of a layer that need this projection).
 //
+// Products that such tiles would not fill the chip with run in the smaller
+// tiles of gemm_rows.hip (gemm_plan below).
+//
 // A 512-thread workgroup computes a 256 x 256 tile of Y in 64-wide K steps.
 // Eight waves in a 4 x 2 grid each own a 64 x 128 sub-tile as 4 x 8 tiles of
 // v_mfma_f32_16x16x32_f16 with fp32 accumulation.  (f16 rather than bf16
@@ -36,29 +39,24 @@
 // l % 16 with the 8 consecutive k of group l / 16; the accumulator holds rows
 // 4 * (l / 16) + r (r = 0..3) of column l % 16.
 #include <algorithm>
-#include <type_traits>
+#include <cmath>
 
+#include "gemm_rows.h"
 #include "mz_kernels.h"
+#include "q4_dequant.h"
 #include "rope.h"
 #include "rownorm.h"
 
 namespace mzk {
 namespace {
 
-typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
-typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-typedef __attribute__((address_space(3))) void lds_void;
-typedef __attribute__((address_space(1))) void glb_void;
 
-constexpr int BN = kGemmTileN, BK = kGemmTileK;
+constexpr int BM = 256, BN = kGemmTileN, BK = kGemmTileK;
 constexpr int NT = 512;                      // threads
 constexpr int ROW = BK;                      // halves per LDS row (128 B, swizzled)
 constexpr int B_TILE = BN * ROW;             // one 32 KB weight stage (256 x 64)
 constexpr int A_STAGES = 3, B_STAGES = 2;
 constexpr int NIB_BYTES = BN * BK / 2;       // 8192
-
-__device__ __forceinline__ float silu(float g) { return g / (1.0f + __expf(-g)); }
 
 // LDS offset (halves) of logical 16-byte column c of row r
 __device__ __forceinline__ int swz(int r, int c) { return r * ROW + ((c ^ ((r >> 1) & 7)) << 3); }
@@ -66,37 +64,6 @@ __device__ __forceinline__ int swz(int r, int c) { return r * ROW + ((c ^ ((r >>
 __device__ __forceinline__ uint32_t pair_code(uint32_t w, int shift) {
   // two 4-bit codes at bits [shift, shift+4) and [16+shift, 20+shift) -> halves 1024 + q
   return ((w >> shift) & 0x000F000Fu) | 0x64006400u;
-}
-
-// (x & mask) | magic in one instruction (the mask from a scalar register, the
-// magic from a vector register: one scalar operand per VOP3 on this chip)
-__device__ __forceinline__ uint32_t and_or(uint32_t x, uint32_t mask, uint32_t magic) {
-  uint32_t r;
-  asm("v_and_or_b32 %0, %1, %2, %3" : "=v"(r) : "v"(x), "s"(mask), "v"(magic));
-  return r;
-}
-
-// The 8 codes of one pre-ordered dword (pair m at bits 4m and 16 + 4m) ->
-// 4 f16x2 of d * (q - 8), pair m in component m.  The integer-to-half step
-// is the published exponent-bias conversion of 4-bit integers (Kim et al.,
-// arXiv:2211.10017): OR-ing a code into the mantissa of a half whose ulp is 1
-// (or 1/16 for the high nibble) and subtracting the bias gives it exactly.
-__device__ __forceinline__ uint4 dequant_dword(uint32_t w, f16x2 d2) {
-  const uint32_t mag_lo = 0x64006400u;   // 1024: code bits 0-3 add q
-  const uint32_t mag_hi = 0x54005400u;   // 64: code bits 4-7 add q (ulp 1/16)
-  const f16x2 off_lo = {(_Float16)1032.0f, (_Float16)1032.0f};
-  const f16x2 off_hi = {(_Float16)72.0f, (_Float16)72.0f};
-  const uint32_t w8 = w >> 8;
-  const f16x2 c0 = __builtin_bit_cast(f16x2, and_or(w, 0x000F000Fu, mag_lo));
-  const f16x2 c1 = __builtin_bit_cast(f16x2, and_or(w, 0x00F000F0u, mag_hi));
-  const f16x2 c2 = __builtin_bit_cast(f16x2, and_or(w8, 0x000F000Fu, mag_lo));
-  const f16x2 c3 = __builtin_bit_cast(f16x2, and_or(w8, 0x00F000F0u, mag_hi));
-  uint4 o;
-  o.x = __builtin_bit_cast(uint32_t, (c0 - off_lo) * d2);
-  o.y = __builtin_bit_cast(uint32_t, (c1 - off_hi) * d2);
-  o.z = __builtin_bit_cast(uint32_t, (c2 - off_lo) * d2);
-  o.w = __builtin_bit_cast(uint32_t, (c3 - off_hi) * d2);
-  return o;
 }
 
 // One pre-ordered Q4_0 block (4 dwords; dword i holds elements 8i..8i+7) of
@@ -111,13 +78,12 @@ __device__ __forceinline__ void dequant_block_to_lds(uint4 nib, uint16_t dbits, 
     *reinterpret_cast<uint4*>(stage + swz(row, blk * 4 + i)) = dequant_dword(w[i], d2);
 }
 
-// Rotary-embedding epilogue of a wave's 64 x 128 (BM 256) or 16 x 128 (BM 64)
-// accumulator block.  Pair partners c and c + hd/2 of a head sit in tiles j
+// Rotary-embedding epilogue of a wave's 64 x 128 accumulator block.  Pair partners c and c + hd/2 of a head sit in tiles j
 // and j + JO (JO = hd / 32) of the same lane.  Row positions (and slot
 // offsets) are read first, then the (cos, sin) of two 16-row groups at once,
 // then the rotated values are stored: the table reads never wait behind the
 // stores of earlier rows.
-template <int EPI, int BM, int JO>
+template <int EPI, int JO>
 __device__ __forceinline__ void rope_epilogue(const f32x4 (&acc)[BM / 64][8], const GemmRope& ea, void* Y, int M,
                                               int mt, int nt, int wm, int wn, int col_in, int row_in) {
   constexpr int MI = BM / 64, IB = (MI >= 2 && EPI == kEpiRopeQ) ? 2 : 1;   // row groups per table read
@@ -190,7 +156,6 @@ __device__ __forceinline__ void rope_epilogue(const f32x4 (&acc)[BM / 64][8], co
         for (int j = 0; j < 8; ++j) {
           const int col = col0 + j * 16;
           if (col >= rot_end && col < ea.n_valid) {
-            typedef _Float16 f16x4 __attribute__((ext_vector_type(4)));
             *reinterpret_cast<f16x4*>(vt + (int64_t)(col - rot_end) * ea.C * 2) =
                 f16x4{(_Float16)acc[i][j][0], (_Float16)acc[i][j][1], (_Float16)acc[i][j][2], (_Float16)acc[i][j][3]};
           }
@@ -213,15 +178,11 @@ __device__ __forceinline__ void rope_epilogue(const f32x4 (&acc)[BM / 64][8], co
   }
 }
 
-// BM = 256 (large m) or 64 (few row tiles: four times as many workgroups; the
-// arithmetic of every output element is the same, so results do not depend
-// on the choice).
-//
 // Split K (EPI == kEpiPartial): blockIdx.y is a split that takes K steps
 // [y * k_steps, min((y + 1) * k_steps, K / 64)) and stores its fp32 sums in
 // Y as [split][M][N]; gemm_splitk_reduce adds the splits in order and applies
 // the real epilogue.
-template <int EPI, int BM>
+template <int EPI>
 __device__ __forceinline__ void gemm_tile(const _Float16* __restrict__ X, const int32_t* __restrict__ a_rows,
                                           int M, int K, const uint8_t* __restrict__ Wp, int N,
                                           void* __restrict__ Y, int k_steps, const GemmRope& ea, int mt, int nt) {
@@ -363,11 +324,11 @@ __device__ __forceinline__ void gemm_tile(const _Float16* __restrict__ X, const 
   const int row_in = (lane >> 4) * 4;
   if constexpr (EPI == kEpiRopeQ || EPI == kEpiRopeKV) {
     if (ea.hd == 128)
-      rope_epilogue<EPI, BM, 4>(acc, ea, Y, M, mt, nt, wm, wn, col_in, row_in);
+      rope_epilogue<EPI, 4>(acc, ea, Y, M, mt, nt, wm, wn, col_in, row_in);
     else if (ea.hd == 64)
-      rope_epilogue<EPI, BM, 2>(acc, ea, Y, M, mt, nt, wm, wn, col_in, row_in);
+      rope_epilogue<EPI, 2>(acc, ea, Y, M, mt, nt, wm, wn, col_in, row_in);
     else
-      rope_epilogue<EPI, BM, 1>(acc, ea, Y, M, mt, nt, wm, wn, col_in, row_in);
+      rope_epilogue<EPI, 1>(acc, ea, Y, M, mt, nt, wm, wn, col_in, row_in);
     return;
   }
   if constexpr (EPI == kEpiAdd) {
@@ -418,7 +379,7 @@ __device__ __forceinline__ void gemm_tile(const _Float16* __restrict__ X, const 
         for (int jp = 0; jp < 4; ++jp) {
           const float g = acc[i][2 * jp][r], u = acc[i][2 * jp + 1][r];
           const int col = nt * (BN / 2) + wn * 64 + jp * 16 + col_in;
-          y[col] = (_Float16)(silu(g) * u);
+          y[col] = swiglu_f16(g, u);
         }
       } else {
         float* y = reinterpret_cast<float*>(Y) + ((size_t)split * M + row) * N;
@@ -471,7 +432,7 @@ __device__ __forceinline__ int gemm_pop(int* wq, int home, int total) {
 // the XCDs run at clocks several percent apart; with a fixed share each, the
 // slowest one sets the end of the launch.  (Store, add and SwiGLU epilogues;
 // the others always run static.)
-template <int EPI, int BM>
+template <int EPI>
 __global__ __launch_bounds__(NT) void gemm_q4_kernel(const _Float16* __restrict__ X,
                                                      const int32_t* __restrict__ a_rows, int M, int K,
                                                      const uint8_t* __restrict__ Wp, int N,
@@ -508,7 +469,7 @@ __global__ __launch_bounds__(NT) void gemm_q4_kernel(const _Float16* __restrict_
       const int per = (int)gridDim.x / 8;
       t = b < per * 8 ? (b % 8) * per + b / 8 : b;
     }
-    gemm_tile<EPI, BM>(X, a_rows, M, K, Wp, N, Y, k_steps, ea, t / n_tiles, t % n_tiles);
+    gemm_tile<EPI>(X, a_rows, M, K, Wp, N, Y, k_steps, ea, t / n_tiles, t % n_tiles);
   }
   if (!persistent) return;
   if (threadIdx.x == 0 && atomicAdd(&wq[kGemmWqDone], 1) == (int)gridDim.x - 1) {
@@ -605,6 +566,26 @@ __global__ __launch_bounds__(256) void gemv_q4_kernel(const _Float16* __restrict
   part[(size_t)split * N + (size_t)nt * BN + r] = acc;
 }
 
+// The sum over the K splits, in split order, of V (float or f32x4) at p, p +
+// plane, ...  kReduceAhead loads go out together, from split indices clamped
+// into range: one load at a time, the reduce took a memory round trip per
+// split (8B down projection, 17 rows in 16 splits: 6.0 us against 3.1, the
+// launch included).
+constexpr int kReduceAhead = 8;
+template <typename V>
+__device__ __forceinline__ V split_sum(const float* p, int ns, size_t plane) {
+  V a = *reinterpret_cast<const V*>(p);
+  for (int s0 = 1; s0 < ns; s0 += kReduceAhead) {
+    V b[kReduceAhead];
+#pragma unroll
+    for (int u = 0; u < kReduceAhead; ++u) b[u] = *reinterpret_cast<const V*>(p + (size_t)min(s0 + u, ns - 1) * plane);
+#pragma unroll
+    for (int u = 0; u < kReduceAhead; ++u)
+      if (s0 + u < ns) a += b[u];
+  }
+  return a;
+}
+
 // Sum of the K splits in split order, then the epilogue; 4 columns per
 // thread (SwiGLU: 4 output columns, whose gate and up sums are 4 consecutive
 // columns each: output column o takes gate column 32 (o / 16) + o % 16 and the
@@ -620,31 +601,17 @@ __global__ __launch_bounds__(256) void gemm_splitk_reduce(const float* __restric
   if constexpr (EPI == kEpiSwiGLU) {
     const int cg = 32 * (o / 16) + o % 16;
     const float* pg = part + (size_t)row * N + cg;
-    float4 g = *reinterpret_cast<const float4*>(pg), u = *reinterpret_cast<const float4*>(pg + 16);
-    for (int sp = 1; sp < ns; ++sp) {
-      const float4 g2 = *reinterpret_cast<const float4*>(pg + sp * plane);
-      const float4 u2 = *reinterpret_cast<const float4*>(pg + sp * plane + 16);
-      g.x += g2.x; g.y += g2.y; g.z += g2.z; g.w += g2.w;
-      u.x += u2.x; u.y += u2.y; u.z += u2.z; u.w += u2.w;
-    }
+    const f32x4 g = split_sum<f32x4>(pg, ns, plane), u = split_sum<f32x4>(pg + 16, ns, plane);
     _Float16* y = reinterpret_cast<_Float16*>(Y) + (size_t)row * NO + o;
-    y[0] = (_Float16)(silu(g.x) * u.x);
-    y[1] = (_Float16)(silu(g.y) * u.y);
-    y[2] = (_Float16)(silu(g.z) * u.z);
-    y[3] = (_Float16)(silu(g.w) * u.w);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) y[e] = (_Float16)(silu(g[e]) * u[e]);
   } else {
     const float* pp = part + (size_t)row * N + o;
-    float4 a = *reinterpret_cast<const float4*>(pp);
-    for (int sp = 1; sp < ns; ++sp) {
-      const float4 b = *reinterpret_cast<const float4*>(pp + sp * plane);
-      a.x += b.x; a.y += b.y; a.z += b.z; a.w += b.w;
-    }
-    float4* y = reinterpret_cast<float4*>(reinterpret_cast<float*>(Y) + (size_t)row * N + o);
-    if (EPI == kEpiAdd) {
-      const float4 c = *y;
-      a.x += c.x; a.y += c.y; a.z += c.z; a.w += c.w;
-    }
-    *y = a;
+    f32x4* y = reinterpret_cast<f32x4*>(reinterpret_cast<float*>(Y) + (size_t)row * N + o);
+    f32x4 c = {};
+    if (EPI == kEpiAdd) c = *y;
+    const f32x4 a = split_sum<f32x4>(pp, ns, plane);
+    *y = EPI == kEpiAdd ? a + c : a;
   }
 }
 
@@ -668,11 +635,7 @@ __global__ __launch_bounds__(256) void gemm_splitk_reduce_rope(const float* __re
   const float* pr = part + (size_t)row * N;
   if (j < pairs) {
     const int i = j % half, c = (j / half) * ea.hd + i;
-    float x1 = pr[c], x2 = pr[c + half];
-    for (int sp = 1; sp < ns; ++sp) {
-      x1 += pr[sp * plane + c];
-      x2 += pr[sp * plane + c + half];
-    }
+    const float x1 = split_sum<float>(pr + c, ns, plane), x2 = split_sum<float>(pr + c + half, ns, plane);
     const float2 cv = ea.rope_cs[(size_t)p * half + i];
     _Float16* yr = EPI == kEpiRopeQ ? reinterpret_cast<_Float16*>(Y) + (size_t)row * ea.n_valid
                                     : reinterpret_cast<_Float16*>(ea.slab + off);
@@ -681,8 +644,7 @@ __global__ __launch_bounds__(256) void gemm_splitk_reduce_rope(const float* __re
     yr[c + half] = (_Float16)y.y;
   } else {
     const int v = j - pairs;
-    float a = pr[rot + v];
-    for (int sp = 1; sp < ns; ++sp) a += pr[sp * plane + rot + v];
+    const float a = split_sum<float>(pr + rot + v, ns, plane);
     const int pc = p & (ea.C - 1);
     uint8_t* vt = ea.slab + off - (int64_t)pc * ea.n_valid + (int64_t)ea.C * ea.n_valid + pc * 2;
     *reinterpret_cast<_Float16*>(vt + (int64_t)v * ea.C * 2) = (_Float16)a;
@@ -969,22 +931,19 @@ __global__ __launch_bounds__(256) void gemv1_qkv_kernel(int g_q, const _Float16*
                                                 lds);
 }
 
-template <int BM>
-constexpr size_t lds_bytes() {
-  return ((size_t)A_STAGES * BM * ROW + (size_t)B_STAGES * B_TILE) * sizeof(_Float16);
-}
+constexpr size_t kLdsBytes = ((size_t)A_STAGES * BM * ROW + (size_t)B_STAGES * B_TILE) * sizeof(_Float16);
 
 // Rounds of resident workgroups from which a launch takes its tiles from the
 // work queues (measured on the 8B projections: +3.6 % at 56 rounds, none at 8).
 constexpr int kQueueMinRounds = 16;
 
-template <int EPI, int BM>
-void launch_bm(const _Float16* X, const int32_t* a_rows, int m, int n, int k, const uint8_t* W, void* y,
-               hipStream_t s, int n_split = 1, int k_steps = 0, const GemmRope& ea = GemmRope{},
-               int* wq = nullptr) {
+template <int EPI>
+void launch_tiles(const _Float16* X, const int32_t* a_rows, int m, int n, int k, const uint8_t* W, void* y,
+                  hipStream_t s, int n_split = 1, int k_steps = 0, const GemmRope& ea = GemmRope{},
+                  int* wq = nullptr) {
   static const bool lds_ok = [] {   // more than 64 KB of dynamic LDS, once per instantiation
-    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_q4_kernel<EPI, BM>),
-                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes<BM>());
+    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_q4_kernel<EPI>),
+                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLdsBytes);
     return true;
   }();
   (void)lds_ok;
@@ -999,7 +958,7 @@ void launch_bm(const _Float16* X, const int32_t* a_rows, int m, int n, int k, co
           hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0)
         cus = 256;
       if (hipOccupancyMaxActiveBlocksPerMultiprocessor(
-              &per, reinterpret_cast<const void*>(&gemm_q4_kernel<EPI, BM>), NT, lds_bytes<BM>()) != hipSuccess ||
+              &per, reinterpret_cast<const void*>(&gemm_q4_kernel<EPI>), NT, kLdsBytes) != hipSuccess ||
           per <= 0)
         per = 1;
       return cus * per;
@@ -1011,11 +970,9 @@ void launch_bm(const _Float16* X, const int32_t* a_rows, int m, int n, int k, co
     else
       blocks = resident;
   }
-  hipLaunchKernelGGL((gemm_q4_kernel<EPI, BM>), dim3(blocks, n_split), dim3(NT), lds_bytes<BM>(), s, X, a_rows,
-                     m, k, W, n, y, k_steps, ea, wq);
+  hipLaunchKernelGGL((gemm_q4_kernel<EPI>), dim3(blocks, n_split), dim3(NT), kLdsBytes, s, X, a_rows, m, k, W, n, y,
+                     k_steps, ea, wq);
 }
-
-int gemm_row_tile(int m, int n) { return (n / BN) * ((m + 255) / 256) < 128 ? 64 : 256; }
 
 int device_cus() {
   static const int cus = [] {
@@ -1028,36 +985,142 @@ int device_cus() {
   return cus;
 }
 
-// Output rows [r0, r0 + m) of the product: the row-indexed pointers (row
-// list or activations, output, RoPE positions and slot offsets) are shifted.
-template <int EPI, int BM>
-void launch_rows(const _Float16* X, const int32_t* a_rows, int r0, int m, int n, int k, const uint8_t* W, void* y,
-                 hipStream_t s, const GemmRope& ea, int* wq) {
-  const _Float16* x = a_rows ? X : X + (size_t)r0 * k;
-  const int32_t* ar = a_rows ? a_rows + r0 : nullptr;
-  GemmRope e = ea;
-  if (e.pos) e.pos += r0;
-  if (e.kv_off) e.kv_off += r0;
-  void* yy = y;
-  if (EPI == kEpiSwiGLU)
-    yy = reinterpret_cast<_Float16*>(y) + (size_t)r0 * (n / 2);
-  else if (EPI == kEpiRopeQ)
-    yy = reinterpret_cast<_Float16*>(y) + (size_t)r0 * ea.n_valid;
-  else if (EPI == kEpiStore || EPI == kEpiAdd)
-    yy = reinterpret_cast<float*>(y) + (size_t)r0 * n;
-  launch_bm<EPI, BM>(x, ar, m, n, k, W, yy, s, 1, 0, e, wq);
+int gemm_k_steps(int k, int n_split) {
+  const int nk = k / BK;
+  return (nk + n_split - 1) / n_split;
 }
 
-// Relative duration of a 64-row tile against a 256-row one (a quarter of the
-// MFMA work, the same weight traffic and dequantization).
-constexpr double kTile64Cost = 0.35;
+// splits that a split count of n_split leaves non-empty
+int gemm_splits(int k, int n_split) {
+  const int ks = gemm_k_steps(k, n_split);
+  return (k / BK + ks - 1) / ks;
+}
 
-// Rows [r0, r0 + m) of the product split over K (partials in ws, then the
-// reduce with the epilogue): for a remainder of few rows whose tiles alone
-// would leave most of the CUs idle while each runs the whole K range.
+// ---- which tiles, and how many K splits
+//
+// A product runs as 256 x 256 tiles (row_tile 256, this file) or as 32-, 64-
+// or 128-row tiles of 128 columns (gemm_rows.hip), each whole or split over K
+// (fp32 partials and a reduce).  The choice is the smallest of the modelled
+// times below: K steps of 64 per workgroup, times the time of a step at that
+// many resident workgroups, plus what the output and the partials move at 5
+// TB/s, plus fixed costs.  The 256-row tiles do the least dequantization and
+// LDS traffic per product and win where they fill whole rounds of the CUs
+// (8B gate/up, 8320 rows: 1685 us against 1837 as 128-row tiles); elsewhere
+// smaller tiles fill the chip (1.5B down projection, 4979 rows, 120 tiles of
+// 256 rows: 213 us before as 64-row tiles of 256 columns, 137 now as 128-row
+// tiles).  Step times measured on one MI355X with weights from HBM, in us:
+// row_tile 32: 0.34 with one workgroup per CU, 0.56 with two (64-row: 0.40,
+// 0.68; 128-row: 0.56, 0.97); 256-row: 1.42 on half of the CUs, 1.70 on all.
+struct GemmPlan {
+  int row_tile = 256, n_split = 1;
+  double us = 1e30;
+};
+
+// kSecondUs: the second workgroup of a CU starts behind the first
+constexpr double kLaunchUs = 3.0, kSecondUs = 1.0, kReduceUs = 3.2, kBytesPerUs = 5e6;
+constexpr int kMinSplitSteps = 4;
+
+double plan_us(int m, int n, int k, int row_tile, int ns) {
+  const double cus = device_cus();
+  const int bn = row_tile == 256 ? BN : 128;
+  const double w = (double)(n / bn) * ((m + row_tile - 1) / row_tile) * ns;
+  double t_lo, t_hi;   // a step at one workgroup per CU (256-row: on half of the CUs) and with the chip full
+  switch (row_tile) {
+    case 32: t_lo = 0.34, t_hi = 0.56; break;
+    case 64: t_lo = 0.40, t_hi = 0.68; break;
+    case 128: t_lo = 0.56, t_hi = 0.97; break;
+    default: t_lo = 1.42, t_hi = 1.70; break;
+  }
+  const double round = row_tile == 256 ? cus : 2 * cus;
+  const double full = std::floor(w / round), rem = w - full * round;
+  double steps = full * t_hi;
+  if (rem > 0) steps += rem <= round / 2 ? t_lo : t_lo + (t_hi - t_lo) * (rem - round / 2) / (round / 2);
+  const double out = (double)ns * m * n * 4 / kBytesPerUs;
+  const double second = row_tile < 256 && w > cus ? kSecondUs : 0.;
+  return kLaunchUs + second + gemm_k_steps(k, ns) * steps + out + (ns > 1 ? kReduceUs + out : 0.);
+}
+
+// The plan of a product of m rows with at most max_split splits whose
+// partials fit ws_cap bytes.  rows_ok: the smaller tiles may run.
+GemmPlan gemm_plan(int m, int n, int k, int64_t ws_cap, int max_split, bool rows_ok) {
+  static const int kSplits[] = {1, 2, 3, 4, 6, 8, 12, 16, 24, 32};
+  GemmPlan best;
+  const int nk = k / BK;
+  // with many rounds of 256-row tiles nothing smaller pays
+  const bool many = (int64_t)(n / BN) * (m / BM) >= 4 * (int64_t)device_cus();
+  for (int row_tile : {256, 128, 64, 32}) {
+    if (row_tile < 256 && (!rows_ok || many)) break;
+    if (row_tile > 32 && row_tile < 256 && row_tile >= 2 * m) continue;
+    for (int want : kSplits) {
+      if (want > max_split || (want > 1 && nk / want < kMinSplitSteps)) break;
+      const int ns = gemm_splits(k, want);
+      if (ns > 1 && gemm_splitk_ws_bytes(m, n, ns) > ws_cap) break;
+      const double us = plan_us(m, n, k, row_tile, ns);
+      if (us < best.us) best = GemmPlan{row_tile, ns, us};
+    }
+  }
+  return best;
+}
+
+// What the vector stores of the small tiles need of the output: 16-byte
+// alignment (fp32) or 8-byte (f16), whole heads of rotated columns, and slots
+// and queries off the 4-column groups' way.
+bool gemm_rows_ok(int epilogue, const void* y, const GemmRope& ea) {
+  const uintptr_t a = reinterpret_cast<uintptr_t>(y);
+  switch (epilogue) {
+    case kEpiSwiGLU: return (a & 7) == 0;
+    case kEpiRopeQ: return (a & 7) == 0 && ea.n_valid % ea.hd == 0;
+    case kEpiRopeKV: return ea.n_valid % (2 * ea.hd) == 0;
+    default: return (a & 15) == 0;
+  }
+}
+
+// Splits of one product as partials in ws; returns how many were written.
+int launch_partials(const void* x, int m, int n, int k, const void* w, int n_split, void* ws, hipStream_t s,
+                    const int32_t* a_rows, const float* h_norm, float eps, int row_tile) {
+  const _Float16* X = reinterpret_cast<const _Float16*>(x);
+  const uint8_t* W = reinterpret_cast<const uint8_t*>(w);
+  const int ks = gemm_k_steps(k, n_split), ns = gemm_splits(k, n_split);
+  if (h_norm)
+    hipLaunchKernelGGL(gemv_q4_kernel<true>, dim3(n / BN, ns), dim3(256), 0, s, X, h_norm, eps, a_rows, k, W, n,
+                       reinterpret_cast<float*>(ws), ks);
+  else if (m == 1)
+    hipLaunchKernelGGL(gemv_q4_kernel<false>, dim3(n / BN, ns), dim3(256), 0, s, X, nullptr, 0.f, a_rows, k, W,
+                       n, reinterpret_cast<float*>(ws), ks);
+  else if (row_tile == 256)
+    launch_tiles<kEpiPartial>(X, a_rows, m, n, k, W, ws, s, ns, ks);
+  else
+    launch_gemm_rows(x, a_rows, m, n, k, w, kEpiPartial, ws, s, row_tile, ns, ks);
+  return ns;
+}
+
+// The reduce of ns partials with the epilogue.
+void launch_reduce(const float* part, int ns, int m, int n, int epilogue, const GemmRope& ea, void* y, hipStream_t s) {
+  if (epilogue == kEpiRopeQ || epilogue == kEpiRopeKV) {
+    const int rot = epilogue == kEpiRopeQ ? ea.n_valid : ea.n_valid / 2;
+    const int64_t per_row = rot / 2 + (epilogue == kEpiRopeKV ? ea.n_valid / 2 : 0);
+    const dim3 grid((unsigned)(((int64_t)m * per_row + 255) / 256));
+    if (epilogue == kEpiRopeQ)
+      hipLaunchKernelGGL(gemm_splitk_reduce_rope<kEpiRopeQ>, grid, dim3(256), 0, s, part, ns, m, n, ea, y);
+    else
+      hipLaunchKernelGGL(gemm_splitk_reduce_rope<kEpiRopeKV>, grid, dim3(256), 0, s, part, ns, m, n, ea, y);
+    return;
+  }
+  const int64_t outs = (int64_t)m * (epilogue == kEpiSwiGLU ? n / 2 : n) / 4;
+  const dim3 grid((unsigned)((outs + 255) / 256));
+  switch (epilogue) {
+    case kEpiStore: hipLaunchKernelGGL(gemm_splitk_reduce<kEpiStore>, grid, dim3(256), 0, s, part, ns, m, n, y); break;
+    case kEpiAdd: hipLaunchKernelGGL(gemm_splitk_reduce<kEpiAdd>, grid, dim3(256), 0, s, part, ns, m, n, y); break;
+    default: hipLaunchKernelGGL(gemm_splitk_reduce<kEpiSwiGLU>, grid, dim3(256), 0, s, part, ns, m, n, y); break;
+  }
+}
+
+// Output rows [r0, r0 + m) of the product by a plan: the row-indexed
+// pointers (row list or activations, output, RoPE positions and slot offsets)
+// are shifted.
 template <int EPI>
-void launch_rows_split(const _Float16* X, const int32_t* a_rows, int r0, int m, int n, int k, const uint8_t* W,
-                       void* y, hipStream_t s, const GemmRope& ea, void* ws, int ns, int row_tile = 0) {
+void launch_planned(const GemmPlan& plan, const _Float16* X, const int32_t* a_rows, int r0, int m, int n, int k,
+                    const uint8_t* W, void* y, hipStream_t s, const GemmRope& ea, int* wq, void* ws) {
   const _Float16* x = a_rows ? X : X + (size_t)r0 * k;
   const int32_t* ar = a_rows ? a_rows + r0 : nullptr;
   GemmRope e = ea;
@@ -1070,54 +1133,37 @@ void launch_rows_split(const _Float16* X, const int32_t* a_rows, int r0, int m, 
     yy = reinterpret_cast<_Float16*>(y) + (size_t)r0 * ea.n_valid;
   else if (EPI == kEpiStore || EPI == kEpiAdd)
     yy = reinterpret_cast<float*>(y) + (size_t)r0 * n;
-  if (EPI == kEpiRopeQ || EPI == kEpiRopeKV)
-    launch_gemm_q4_splitk_rope(x, m, n, k, W, EPI, e, yy, ns, ws, s, ar, nullptr, 0.f, row_tile);
-  else
-    launch_gemm_q4_splitk(x, m, n, k, W, EPI, yy, ns, ws, s, ar, nullptr, 0.f, row_tile);
+  if (plan.n_split > 1) {
+    const int ns = launch_partials(x, m, n, k, W, plan.n_split, ws, s, ar, nullptr, 0.f, plan.row_tile);
+    launch_reduce(reinterpret_cast<const float*>(ws), ns, m, n, EPI, e, yy, s);
+  } else if (plan.row_tile == 256) {
+    launch_tiles<EPI>(x, ar, m, n, k, W, yy, s, 1, 0, e, wq);
+  } else {
+    launch_gemm_rows(x, ar, m, n, k, W, EPI, yy, s, plan.row_tile, 1, 0, e);
+  }
 }
 
 template <int EPI>
 void launch_epi(const _Float16* X, const int32_t* a_rows, int m, int n, int k, const uint8_t* W, void* y,
                 hipStream_t s, const GemmRope& ea = GemmRope{}, int* wq = nullptr, void* ws = nullptr,
-                int64_t ws_bytes = 0) {
-  // 256-row tiles unless they leave most of the 256 CUs idle; then 256-row
-  // tiles split over K where the K range is long, else 64-row tiles
-  if (gemm_row_tile(m, n) == 64) {
-    const int ns = ws ? gemm_long_k_splits(m, n, k, ws_bytes) : 1;
-    if (ns > 1)
-      launch_rows_split<EPI>(X, a_rows, 0, m, n, k, W, y, s, ea, ws, ns, 256);
-    else
-      launch_bm<EPI, 64>(X, a_rows, m, n, k, W, y, s, 1, 0, ea, wq);
-    return;
-  }
+                int64_t ws_bytes = 0, int max_split = 32) {
+  const bool ok = gemm_rows_ok(EPI, y, ea);
+  const int ns_cap = ws && ok ? max_split : 1;
+  const GemmPlan whole = gemm_plan(m, n, k, ws_bytes, ns_cap, ok);
   // A ragged last row of 256-row tiles can make a final round of workgroups
   // that occupies few CUs (16 column tiles x 129 row tiles = 8 rounds + 16
   // workgroups on 256 CUs).  Then the whole 256-row tiles run in one launch
-  // and the remaining rows as 64-row tiles in a second one.
-  const int nt = n / BN, cus = device_cus();
-  const int full = m / 256, rem = m - full * 256;
+  // and the remaining rows by a plan of their own in a second one.
+  const int full = m / BM * BM, rem = m - full;
   if (rem > 0 && full > 0) {
-    auto rounds = [&](int tiles) { return (double)((tiles + cus - 1) / cus); };
-    const double one = rounds(nt * (full + 1));
-    const double two = rounds(nt * full) + kTile64Cost * rounds(nt * ((rem + 63) / 64));
-    if (two < one) {
-      launch_rows<EPI, 256>(X, a_rows, 0, full * 256, n, k, W, y, s, ea, wq);
-      // the remainder split over K when a workspace is at hand and its
-      // tiles alone would not fill the chip
-      const int ns = ws ? gemm_auto_splits(rem, n, k, ws_bytes) : 1;
-      if (ns > 1)
-        launch_rows_split<EPI>(X, a_rows, full * 256, rem, n, k, W, y, s, ea, ws, ns);
-      else
-        launch_rows<EPI, 64>(X, a_rows, full * 256, rem, n, k, W, y, s, ea, wq);
+    const GemmPlan tail = gemm_plan(rem, n, k, ws_bytes, ns_cap, ok);
+    if (plan_us(full, n, k, 256, 1) + tail.us < whole.us) {
+      launch_planned<EPI>(GemmPlan{}, X, a_rows, 0, full, n, k, W, y, s, ea, wq, ws);
+      launch_planned<EPI>(tail, X, a_rows, full, rem, n, k, W, y, s, ea, nullptr, ws);
       return;
     }
   }
-  launch_bm<EPI, 256>(X, a_rows, m, n, k, W, y, s, 1, 0, ea, wq);
-}
-
-int gemm_k_steps(int k, int n_split) {
-  const int nk = k / BK;
-  return (nk + n_split - 1) / n_split;
+  launch_planned<EPI>(whole, X, a_rows, 0, m, n, k, W, y, s, ea, wq, ws);
 }
 
 }  // namespace
@@ -1125,61 +1171,28 @@ int gemm_k_steps(int k, int n_split) {
 int64_t gemm_splitk_ws_bytes(int m, int n, int n_split) { return (int64_t)n_split * m * n * 4; }
 
 int gemm_auto_splits(int m, int n, int k, int64_t ws_cap) {
-  const int bm = gemm_row_tile(m, n);
+  const int bm = (n / BN) * ((m + 255) / 256) < 128 ? 64 : 256;
   const int tiles = (n / BN) * ((m + bm - 1) / bm);
   const int nk = k / BK;
   // about two workgroups per CU, at least 4 K steps per split.  From 1024
   // rows on, tiles that cover half the CUs run whole: there the partials and
-  // their reduce cost more than the idle CUs save (K/V of 2048 rows, 1024
-  // outputs, K 2048: 29.3 us whole against 31.1 in 4 splits; of 4979 rows,
-  // 512 outputs, K 1536: 23.1 against 33.6)
+  // their reduce cost more than the idle CUs save
   constexpr int kTarget = 512, kMinSteps = 4, kMaxSplits = 32, kWholeRows = 1024;
   if (tiles >= kTarget / 2 || nk < 2 * kMinSteps || (m >= kWholeRows && tiles >= kTarget / 4)) return 1;
   int ns = std::min({(kTarget + tiles - 1) / tiles, nk / kMinSteps, kMaxSplits});
   while (ns > 1 && gemm_splitk_ws_bytes(m, n, ns) > ws_cap) --ns;
-  if (ns <= 1) return 1;
-  const int ks = gemm_k_steps(k, ns);
-  return (nk + ks - 1) / ks;   // no empty trailing split
+  return ns <= 1 ? 1 : gemm_splits(k, ns);   // no empty trailing split
 }
 
 int gemm_long_k_splits(int m, int n, int k, int64_t ws_cap) {
-  // The 64-row tiles fill the chip, but each dequantizes its weight tiles over
-  // the whole K range for 64 rows.  256-row tiles split over K into one round
-  // of the chip do a quarter of that dequantization per MFMA, which pays for
-  // the fp32 partials and their reduce when each split keeps at least 16 K
-  // steps (2048 x 2048 x 8192: 4 splits of 32 steps).
   constexpr int kMinSteps = 16;
   const int cus = device_cus();
   const int tiles = (n / BN) * ((m + 255) / 256), nk = k / BK;
   if (tiles >= cus || (n / BN) * ((m + 63) / 64) < cus) return 1;
   const int ns = (cus + tiles - 1) / tiles;
   if (ns < 2 || nk / ns < kMinSteps || gemm_splitk_ws_bytes(m, n, ns) > ws_cap) return 1;
-  const int ks = gemm_k_steps(k, ns);
-  return (nk + ks - 1) / ks;
+  return gemm_splits(k, ns);
 }
-
-namespace {
-// The fp32 partials [split][m][n] of a split-K product; returns the number of
-// splits written.
-int launch_partials(const void* x, int m, int n, int k, const void* w, int n_split, void* ws, hipStream_t s,
-                    const int32_t* a_rows, const float* h_norm, float eps, int row_tile) {
-  const _Float16* X = reinterpret_cast<const _Float16*>(x);
-  const uint8_t* W = reinterpret_cast<const uint8_t*>(w);
-  const int ks = gemm_k_steps(k, n_split);
-  const int ns = (k / BK + ks - 1) / ks;
-  if (h_norm)
-    hipLaunchKernelGGL(gemv_q4_kernel<true>, dim3(n / BN, ns), dim3(256), 0, s, X, h_norm, eps, a_rows, k, W, n,
-                       reinterpret_cast<float*>(ws), ks);
-  else if (m == 1)
-    hipLaunchKernelGGL(gemv_q4_kernel<false>, dim3(n / BN, ns), dim3(256), 0, s, X, nullptr, 0.f, a_rows, k, W,
-                       n, reinterpret_cast<float*>(ws), ks);
-  else if ((row_tile ? row_tile : gemm_row_tile(m, n)) == 64)
-    launch_bm<kEpiPartial, 64>(X, a_rows, m, n, k, W, ws, s, ns, ks);
-  else
-    launch_bm<kEpiPartial, 256>(X, a_rows, m, n, k, W, ws, s, ns, ks);
-  return ns;
-}
-}  // namespace
 
 namespace {
 template <bool NORM, int EPI, int CPW>
@@ -1240,31 +1253,38 @@ void launch_gemv1(const void* x, int n, int k, const void* w, int epilogue, cons
   }
 }
 
+namespace {
+
+template <int EPI>
+void launch_splitk(const void* x, int m, int n, int k, const void* w, const GemmRope& ea, void* y, int n_split,
+                   void* ws, hipStream_t s, const int32_t* a_rows, const float* h_norm, float eps) {
+  if (m == 1) {   // the split GEMV
+    const int ns = launch_partials(x, m, n, k, w, n_split, ws, s, a_rows, h_norm, eps, 0);
+    launch_reduce(reinterpret_cast<const float*>(ws), ns, m, n, EPI, ea, y, s);
+    return;
+  }
+  launch_epi<EPI>(reinterpret_cast<const _Float16*>(x), a_rows, m, n, k, reinterpret_cast<const uint8_t*>(w), y, s, ea,
+                  nullptr, ws, gemm_splitk_ws_bytes(m, n, n_split), n_split);
+}
+
+}  // namespace
+
 void launch_gemm_q4_splitk_rope(const void* x, int m, int n, int k, const void* w, int epilogue, const GemmRope& ea,
                                 void* y, int n_split, void* ws, hipStream_t s, const int32_t* a_rows,
-                                const float* h_norm, float eps, int row_tile) {
-  const int ns = launch_partials(x, m, n, k, w, n_split, ws, s, a_rows, h_norm, eps, row_tile);
-  const int rot = epilogue == kEpiRopeQ ? ea.n_valid : ea.n_valid / 2;
-  const int64_t per_row = rot / 2 + (epilogue == kEpiRopeKV ? ea.n_valid / 2 : 0);
-  const dim3 grid((unsigned)(((int64_t)m * per_row + 255) / 256));
-  const float* part = reinterpret_cast<const float*>(ws);
+                                const float* h_norm, float eps) {
   if (epilogue == kEpiRopeQ)
-    hipLaunchKernelGGL(gemm_splitk_reduce_rope<kEpiRopeQ>, grid, dim3(256), 0, s, part, ns, m, n, ea, y);
+    launch_splitk<kEpiRopeQ>(x, m, n, k, w, ea, y, n_split, ws, s, a_rows, h_norm, eps);
   else
-    hipLaunchKernelGGL(gemm_splitk_reduce_rope<kEpiRopeKV>, grid, dim3(256), 0, s, part, ns, m, n, ea, y);
+    launch_splitk<kEpiRopeKV>(x, m, n, k, w, ea, y, n_split, ws, s, a_rows, h_norm, eps);
 }
 
 void launch_gemm_q4_splitk(const void* x, int m, int n, int k, const void* w, int epilogue, void* y, int n_split,
-                           void* ws, hipStream_t s, const int32_t* a_rows, const float* h_norm, float eps,
-                           int row_tile) {
-  const int ns = launch_partials(x, m, n, k, w, n_split, ws, s, a_rows, h_norm, eps, row_tile);
-  const int64_t outs = (int64_t)m * (epilogue == kEpiSwiGLU ? n / 2 : n) / 4;
-  const dim3 grid((unsigned)((outs + 255) / 256));
-  const float* part = reinterpret_cast<const float*>(ws);
+                           void* ws, hipStream_t s, const int32_t* a_rows, const float* h_norm, float eps) {
+  const GemmRope ea;
   switch (epilogue) {
-    case kEpiStore: hipLaunchKernelGGL(gemm_splitk_reduce<kEpiStore>, grid, dim3(256), 0, s, part, ns, m, n, y); break;
-    case kEpiAdd: hipLaunchKernelGGL(gemm_splitk_reduce<kEpiAdd>, grid, dim3(256), 0, s, part, ns, m, n, y); break;
-    default: hipLaunchKernelGGL(gemm_splitk_reduce<kEpiSwiGLU>, grid, dim3(256), 0, s, part, ns, m, n, y); break;
+    case kEpiStore: launch_splitk<kEpiStore>(x, m, n, k, w, ea, y, n_split, ws, s, a_rows, h_norm, eps); break;
+    case kEpiAdd: launch_splitk<kEpiAdd>(x, m, n, k, w, ea, y, n_split, ws, s, a_rows, h_norm, eps); break;
+    default: launch_splitk<kEpiSwiGLU>(x, m, n, k, w, ea, y, n_split, ws, s, a_rows, h_norm, eps); break;
   }
 }
 

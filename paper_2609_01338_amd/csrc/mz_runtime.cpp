@@ -393,10 +393,10 @@ const char* kKindName[kKCount] = {"embed_q4", "rmsnorm", "gemm_q4_kv", "rope_kv"
                                   "gemm_q4_qkv_one_row"};
 // HIP kernel symbol each kind launches (to line up with profiler summaries;
 // the Q and K/V projections name their unsplit RoPE-epilogue form)
-const char* kKindKernel[kKCount] = {"embed_kernel", "rmsnorm_kernel", "gemm_q4_kernel<5>",
-                                    "rope_kv_kernel", "gemm_q4_kernel<4>", "rope_kv_kernel",
-                                    "gather_rows_kernel", "attn_kernel", "gemm_q4_kernel<1>",
-                                    "gemm_q4_kernel<2>", "gemm_q4_kernel<1>",
+const char* kKindKernel[kKCount] = {"embed_kernel", "rmsnorm_kernel", "gemm_q4_kernel<5>|gemm_rows_kernel<5>",
+                                    "rope_kv_kernel", "gemm_q4_kernel<4>|gemm_rows_kernel<4>", "rope_kv_kernel",
+                                    "gather_rows_kernel", "attn_kernel", "gemm_q4_kernel<1>|gemm_rows_kernel<1>",
+                                    "gemm_q4_kernel<2>|gemm_rows_kernel<2>", "gemm_q4_kernel<1>|gemm_rows_kernel<1>",
                                     "lm_head_kernel+argmax_kernel",
                                     "attn_kernel<split>|attn_few_kernel+attn_merge_wide_kernel",
                                     "gemv1_qkv_kernel"};
@@ -516,16 +516,17 @@ struct mz_ctx {
   bool fuse_rope = true;             // option fuse_rope: RoPE (and the KV slot writes) in the GEMM epilogue
   bool fuse_norm = true;             // option fuse_norm: a single row's RMSNorm inside its split-K GEMVs
 
-  // Y = X W^T on the compute stream, split over K when the tile grid alone
-  // would leave most of the GPU idle.  hn: X is RMSNorm(hn) formed inside the
-  // product (only where norm_in_gemv(m, n, k)).
+  // Y = X W^T on the compute stream; with gemm_split, split over K where that
+  // is faster (launch_gemm_q4's plan; a single row off the one-launch GEMV by
+  // gemm_auto_splits).  hn: X is RMSNorm(hn) formed inside the product (only
+  // where norm_in_gemv(m, n, k)).
   void gemm(const void* X, int m, int n, int k, const uint8_t* W, int epi, void* Y, hipStream_t s,
             const int32_t* rows = nullptr, const float* hn = nullptr) {
     if (gemv_one(m, n, k)) {
       mzk::launch_gemv1(X, n, k, W, epi, mzk::GemmRope{}, Y, s, rows, hn, cfg.rms_eps);
       return;
     }
-    const int ns = gemm_split ? mzk::gemm_auto_splits(m, n, k, split_ws_bytes) : 1;
+    const int ns = gemm_split && m == 1 ? mzk::gemm_auto_splits(m, n, k, split_ws_bytes) : 1;
     if (ns > 1)
       mzk::launch_gemm_q4_splitk(X, m, n, k, W, epi, Y, ns, split_ws, s, rows, hn, cfg.rms_eps);
     else
@@ -542,7 +543,7 @@ struct mz_ctx {
       mzk::launch_gemv1(X, n, k, W, epi, ea, Y, s, rows, hn, cfg.rms_eps);
       return true;
     }
-    const int ns = gemm_split ? mzk::gemm_auto_splits(m, n, k, split_ws_bytes) : 1;
+    const int ns = gemm_split && m == 1 ? mzk::gemm_auto_splits(m, n, k, split_ws_bytes) : 1;
     if (ns > 1)
       mzk::launch_gemm_q4_splitk_rope(X, m, n, k, W, epi, ea, Y, ns, split_ws, s, rows, hn, cfg.rms_eps);
     else

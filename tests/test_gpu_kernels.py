@@ -322,6 +322,57 @@ def test_gemm_restore_launches(key):
                 assert np.abs(a1 - a2).max() <= 4 * F16_REL * scale, (key, rows_name, epi)
 
 
+@pytest.mark.parametrize("epi,hd", [(0, 0), (1, 0), (2, 0), (4, 32), (4, 64), (4, 128), (5, 32), (5, 64), (5, 128)])
+def test_gemm_tile_heights_same_bits(epi, hd):
+    """A product's first rows by themselves -- so few that they run as 32-, 64-
+    or 128-row tiles -- against the same rows of a product that fills the
+    chip with 256-row tiles: bit for bit, with every epilogue, an odd number
+    of 64-wide K steps, row counts at the edges of every tile height, a row
+    list, and (keys and values) rows that write nothing and positions that
+    do not start on a slot."""
+    torch = torch_cuda()
+    M, N, K, C = 4096, 16384, 192, 16
+    gen = torch.Generator(device="cuda").manual_seed(epi * 10 + hd)
+    X = torch.randn(M, K, device="cuda", generator=gen).to(torch.float16)
+    W_ = torch.randint(0, 256, (N // 256, K // 64, 9216), device="cuda", dtype=torch.uint8, generator=gen)
+    sc = (torch.rand(N // 256, K // 64, 512, device="cuda", generator=gen) * 0.01 + 0.01).to(torch.float16)
+    W_[..., 8192:] = sc.view(torch.uint8).view(N // 256, K // 64, 1024)
+    rows = torch.randperm(M, device="cuda", generator=gen).to(torch.int32)
+    pos = torch.arange(5, 5 + M, device="cuda", dtype=torch.int32)
+    slot = C * (N // 2) * 4
+    off = (pos.long() // C) * slot + (pos.long() % C) * (N // 2) * 2
+    off[3::7] = -1
+    cs = torch.randn(M + 5, max(hd // 2, 1), 2, device="cuda", generator=gen)
+    y0 = torch.randn(M, N, device="cuda", generator=gen) if epi < 2 else None
+
+    def run(m):
+        slab = torch.zeros((M + 5 + C) // C * slot // 2, device="cuda", dtype=torch.float16) if epi == 5 else None
+        y = y0[:m].clone() if epi < 2 else torch.zeros(m, N // 2 if epi == 2 else N, device="cuda", dtype=torch.float16)
+        mz.mz_q4_gemm_ex(X.data_ptr(), m, N, K, W_.data_ptr(), epi, 0 if epi == 5 else y.data_ptr(), stream(),
+                         a_rows=rows.data_ptr(), pos=pos.data_ptr(), rope_cs=cs.data_ptr(),
+                         kv_off=off.data_ptr(), slab=slab.data_ptr() if epi == 5 else 0, head_dim=hd, n_valid=N,
+                         chunk_tokens=C)
+        torch.cuda.synchronize()
+        return slab.view(-1, 2, slot // 4) if epi == 5 else y
+
+    full = run(M)
+    assert bool((full != 0).any())
+    for m in (1, 2, 31, 32, 33, 64, 65, 127, 128, 129, 300):
+        got = run(m)
+        if epi != 5:
+            assert torch.equal(got.view(torch.uint8), full[:m].view(torch.uint8)), m
+            continue
+        p = pos[:m].long()
+        written = off[:m] >= 0
+        for half, view in ((0, lambda t: t[:, 0].view(-1, C, N // 2)),
+                           (1, lambda t: t[:, 1].view(-1, N // 2, C).transpose(1, 2))):
+            a, b = view(got), view(full)
+            assert torch.equal(a[p // C, p % C][written], b[p // C, p % C][written]), (m, half)
+            mask = torch.zeros(a.shape[:2], dtype=torch.bool, device="cuda")
+            mask[(p // C)[written], (p % C)[written]] = True
+            assert not bool((a[~mask] != 0).any()), (m, half)      # nothing else was written
+
+
 def _single_row_shapes(key):
     m = W.WORKLOADS[key].model
     ffp = (m.d_ffn + 127) // 128 * 128      # the SwiGLU output width, as the down projection reads it
