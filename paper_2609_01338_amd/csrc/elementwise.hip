@@ -169,7 +169,6 @@ __global__ __launch_bounds__(256) void gather_rows_kernel(const float* __restric
   for (int i = threadIdx.x; i < d / 4; i += 256) t[i] = s[i];
 }
 
-constexpr int LM_ROWS = 256;   // vocabulary rows per block (64 per wave)
 constexpr int LM_GROUP = 4;    // rows whose codes are in flight together per wave
 
 // logits[v] = x . W_lm[v] with x = RMSNorm(h_last); per-block (max, lowest
@@ -178,9 +177,18 @@ constexpr int LM_GROUP = 4;    // rows whose codes are in flight together per wa
 // (read once from global memory), so the row loop touches no LDS.  With
 // codes q in 0..15, x . d (q - 8) over a block = d (sum x q - 8 sum x), the
 // block's sum of x being precomputed; nibbles become floats with the
-// byte-to-float conversions.  A wave takes its 64 rows LM_GROUP at a time,
-// with two groups in flight: the loads of the next group are issued before
-// the current one is summed.
+// byte-to-float conversions.  A wave takes rows_wave consecutive rows,
+// LM_GROUP at a time, with two groups in flight: the loads of the next group
+// are issued before the current one is summed.
+//
+// Bound by the weight stream, and by how many waves share it: the rows per
+// block are chosen so that the blocks just fill the chip at the kernel's
+// occupancy (a fixed 256 rows left half of it idle at 32000 x 4096, 53.7 ->
+// 26.6 us, and put the 1024 rows of the smallest model on 4 blocks, 31.7 ->
+// 5.9 us; 128256 x 2048 48.5 -> 40.7 us).  The four
+// sums of a group are reduced together, each exchange halving the rows a lane
+// carries (7 exchanges for 24).  The logits leave as one 256-byte store per
+// 64 rows, so they can go straight to pinned host memory.
 // byte K of v as a float (one v_cvt_f32_ubyteK)
 template <int K>
 __device__ __forceinline__ float ubyte_f32(uint32_t v) { return (float)((v >> (8 * K)) & 0xFFu); }
@@ -189,7 +197,7 @@ template <int NBL>
 __global__ __launch_bounds__(256) void lm_head_kernel(const float* __restrict__ h_last, int d,
                                                       float eps, const uint8_t* __restrict__ nib,
                                                       const uint16_t* __restrict__ scale,
-                                                      int vocab, float* __restrict__ logits,
+                                                      int vocab, int rows_wave, float* __restrict__ logits,
                                                       float* __restrict__ part_val,
                                                       int32_t* __restrict__ part_idx) {
   __shared__ float red[4];
@@ -226,7 +234,7 @@ __global__ __launch_bounds__(256) void lm_head_kernel(const float* __restrict__ 
   }
   float best = -INFINITY;
   int32_t best_i = 0x7fffffff;
-  const int v0 = blockIdx.x * LM_ROWS + w * (LM_ROWS / 4);
+  const int v0 = (blockIdx.x * 4 + w) * rows_wave;
   // codes and scales of rows g .. g + LM_GROUP - 1 of this wave, from indices
   // clamped into range (blocks past the row's end read its last block and
   // meet x = 0; rows past the vocabulary read its last row and are not kept)
@@ -242,10 +250,12 @@ __global__ __launch_bounds__(256) void lm_head_kernel(const float* __restrict__ 
       }
     }
   };
+  float mine = 0.f;            // the logit of row 64 i + lane of the wave, stored per 64 rows
   auto dot_group = [&](int g, const uint4 (&q)[LM_GROUP][NBL], const uint16_t (&sc)[LM_GROUP][NBL]) {
+    float a[LM_GROUP];
 #pragma unroll
     for (int k = 0; k < LM_GROUP; ++k) {
-      float acc = 0.f;
+      a[k] = 0.f;
 #pragma unroll
       for (int j = 0; j < NBL; ++j) {
         const uint32_t wd[4] = {q[k][j].x, q[k][j].y, q[k][j].z, q[k][j].w};
@@ -264,29 +274,48 @@ __global__ __launch_bounds__(256) void lm_head_kernel(const float* __restrict__ 
           dot = __builtin_fmaf(xv[j][16 + 4 * i + 3], ubyte_f32<3>(hi), dot);
         }
         const float dd = (float)__builtin_bit_cast(_Float16, sc[k][j]);
-        acc = __builtin_fmaf(dd, __builtin_fmaf(-8.0f, sx[j], dot), acc);
+        a[k] = __builtin_fmaf(dd, __builtin_fmaf(-8.0f, sx[j], dot), a[k]);
       }
-      acc = wave_sum(acc);
-      const int v = v0 + g + k;
-      if (v < vocab) {
-        if (acc > best) {   // rows ascend, so the first maximum keeps the lowest index
-          best = acc;
-          best_i = v;
-        }
-        if (lane == 0) logits[v] = acc;
+    }
+    // lanes 16 r .. 16 r + 15 end with the sum of row g + r
+    const bool h32 = lane & 32, h16 = lane & 16;
+    const float b0 = (h32 ? a[2] : a[0]) + __shfl_xor(h32 ? a[0] : a[2], 32);
+    const float b1 = (h32 ? a[3] : a[1]) + __shfl_xor(h32 ? a[1] : a[3], 32);
+    float c = (h16 ? b1 : b0) + __shfl_xor(h16 ? b0 : b1, 16);
+#pragma unroll
+    for (int o = 8; o > 0; o >>= 1) c += __shfl_xor(c, o);
+    const int v = v0 + g + (lane >> 4);
+    if (v < vocab && c > best) {   // a lane's rows ascend, so the first maximum keeps the lowest index
+      best = c;
+      best_i = v;
+    }
+    if (logits) {
+      const float t = __shfl(c, (lane & 3) * 16);
+      if ((lane & ~3) == (g & 63)) mine = t;
+      if ((g & 63) == 60 || g + LM_GROUP >= rows_wave) {
+        const int g0 = g & ~63;
+        if (g0 + lane < rows_wave && v0 + g0 + lane < vocab) logits[v0 + g0 + lane] = mine;
       }
     }
   };
   // two groups in flight: the next group's codes load while this one is summed
-  static_assert((LM_ROWS / 4) % (2 * LM_GROUP) == 0, "whole group pairs per wave");
   uint4 qa[LM_GROUP][NBL], qb[LM_GROUP][NBL];
   uint16_t sa[LM_GROUP][NBL], sb[LM_GROUP][NBL];
   load_group(0, qa, sa);
-  for (int g = 0; g < LM_ROWS / 4; g += 2 * LM_GROUP) {
+  for (int g = 0; g < rows_wave; g += 2 * LM_GROUP) {
     load_group(g + LM_GROUP, qb, sb);
     dot_group(g, qa, sa);
-    if (g + 2 * LM_GROUP < LM_ROWS / 4) load_group(g + 2 * LM_GROUP, qa, sa);
+    if (g + 2 * LM_GROUP < rows_wave) load_group(g + 2 * LM_GROUP, qa, sa);
     dot_group(g + LM_GROUP, qb, sb);
+  }
+#pragma unroll
+  for (int o = 16; o < 64; o <<= 1) {   // over the four lane groups: larger value, then lower index
+    const float ob = __shfl_xor(best, o);
+    const int32_t oi = __shfl_xor(best_i, o);
+    if (ob > best || (ob == best && oi < best_i)) {
+      best = ob;
+      best_i = oi;
+    }
   }
   if (lane == 0) {
     bval[w] = best;
@@ -308,33 +337,32 @@ __global__ __launch_bounds__(256) void lm_head_kernel(const float* __restrict__ 
 
 __global__ __launch_bounds__(256) void argmax_kernel(const float* __restrict__ val,
                                                      const int32_t* __restrict__ idx, int n,
-                                                     int32_t* __restrict__ token, int32_t* __restrict__ token2) {
-  __shared__ float sv[256];
-  __shared__ int32_t si[256];
+                                                     int32_t* __restrict__ token) {
+  __shared__ float sv[4];
+  __shared__ int32_t si[4];
   float bv = -INFINITY;
   int32_t bi = 0x7fffffff;
-  for (int i = threadIdx.x; i < n; i += 256)
-    if (val[i] > bv || (val[i] == bv && idx[i] < bi)) {
-      bv = val[i];
-      bi = idx[i];
+  auto take = [&](float ov, int32_t oi) {
+    if (ov > bv || (ov == bv && oi < bi)) {
+      bv = ov;
+      bi = oi;
     }
-  sv[threadIdx.x] = bv;
-  si[threadIdx.x] = bi;
-  __syncthreads();
-  for (int s = 128; s > 0; s >>= 1) {
-    if (threadIdx.x < s) {
-      const float ov = sv[threadIdx.x + s];
-      const int32_t oi = si[threadIdx.x + s];
-      if (ov > sv[threadIdx.x] || (ov == sv[threadIdx.x] && oi < si[threadIdx.x])) {
-        sv[threadIdx.x] = ov;
-        si[threadIdx.x] = oi;
-      }
-    }
-    __syncthreads();
+  };
+  for (int i = threadIdx.x; i < n; i += 256) take(val[i], idx[i]);
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) {
+    const float ov = __shfl_xor(bv, o);
+    const int32_t oi = __shfl_xor(bi, o);
+    take(ov, oi);
   }
+  if ((threadIdx.x & 63) == 0) {
+    sv[threadIdx.x >> 6] = bv;
+    si[threadIdx.x >> 6] = bi;
+  }
+  __syncthreads();
   if (threadIdx.x == 0) {
-    *token = si[0];
-    if (token2) *token2 = si[0];
+    for (int i = 1; i < 4; ++i) take(sv[i], si[i]);
+    *token = bi;
   }
 }
 
@@ -379,22 +407,42 @@ void launch_gather_rows(const float* src, const int32_t* idx, int m, int d, floa
   hipLaunchKernelGGL(gather_rows_kernel, dim3(m), dim3(256), 0, s, src, idx, d, dst);
 }
 
+namespace {
+template <int NBL>
+void launch_lm_nbl(const float* h_last, int d, float eps, const uint8_t* w_nib, const uint16_t* w_scale, int vocab,
+                   float* logits, float* part_val, int32_t* part_idx, int32_t* token, hipStream_t s) {
+  static const int resident = [] {   // blocks the chip holds at once
+    int dev = 0, cus = 0, per = 0;
+    if (hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0)
+      cus = 256;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, reinterpret_cast<const void*>(&lm_head_kernel<NBL>), 256,
+                                                     0) != hipSuccess || per <= 0)
+      per = 2;
+    return cus * per;
+  }();
+  const int rows = lm_head_rows(vocab, resident), nblk = (vocab + rows - 1) / rows;
+  hipLaunchKernelGGL(lm_head_kernel<NBL>, dim3(nblk), dim3(256), 0, s, h_last, d, eps, w_nib, w_scale, vocab,
+                     rows / 4, logits, part_val, part_idx);
+  hipLaunchKernelGGL(argmax_kernel, dim3(1), dim3(256), 0, s, part_val, part_idx, nblk, token);
+}
+}  // namespace
+
+int lm_head_rows(int vocab, int blocks) {
+  const int rows = (vocab + blocks - 1) / blocks;
+  return (rows + kLmMinRows - 1) / kLmMinRows * kLmMinRows;
+}
+
 void launch_lm_head(const float* h_last, int d, float eps, const uint8_t* w_nib,
                     const uint16_t* w_scale, int vocab, float* logits, float* part_val,
-                    int32_t* part_idx, int32_t* token, hipStream_t s, int32_t* token2) {
-  const int nblk = (vocab + LM_ROWS - 1) / LM_ROWS;
+                    int32_t* part_idx, int32_t* token, hipStream_t s) {
   const int nbl = (d / 32 + 63) / 64;   // 32-element blocks per lane (d <= 8192)
   switch (nbl) {
-    case 1: hipLaunchKernelGGL(lm_head_kernel<1>, dim3(nblk), dim3(256), 0, s, h_last, d, eps, w_nib, w_scale,
-                               vocab, logits, part_val, part_idx); break;
-    case 2: hipLaunchKernelGGL(lm_head_kernel<2>, dim3(nblk), dim3(256), 0, s, h_last, d, eps, w_nib, w_scale,
-                               vocab, logits, part_val, part_idx); break;
-    case 3: hipLaunchKernelGGL(lm_head_kernel<3>, dim3(nblk), dim3(256), 0, s, h_last, d, eps, w_nib, w_scale,
-                               vocab, logits, part_val, part_idx); break;
-    default: hipLaunchKernelGGL(lm_head_kernel<4>, dim3(nblk), dim3(256), 0, s, h_last, d, eps, w_nib, w_scale,
-                                vocab, logits, part_val, part_idx); break;
+    case 1: launch_lm_nbl<1>(h_last, d, eps, w_nib, w_scale, vocab, logits, part_val, part_idx, token, s); break;
+    case 2: launch_lm_nbl<2>(h_last, d, eps, w_nib, w_scale, vocab, logits, part_val, part_idx, token, s); break;
+    case 3: launch_lm_nbl<3>(h_last, d, eps, w_nib, w_scale, vocab, logits, part_val, part_idx, token, s); break;
+    default: launch_lm_nbl<4>(h_last, d, eps, w_nib, w_scale, vocab, logits, part_val, part_idx, token, s); break;
   }
-  hipLaunchKernelGGL(argmax_kernel, dim3(1), dim3(256), 0, s, part_val, part_idx, nblk, token, token2);
 }
 
 void launch_fill(void* p, int64_t n_words, uint32_t value, hipStream_t s) {

@@ -147,12 +147,16 @@ void launch_embed(const uint8_t* e_nib, const uint16_t* e_scale, const int32_t* 
 void launch_gather_rows(const float* src, const int32_t* idx, int m, int d, float* dst,
                         hipStream_t s);
 
-// logits float [V] = RMSNorm(h_last) . W_lm^T (split layout as the embedding),
-// then token = argmax (lowest index on ties), also stored to token2 when
-// given.  part_val/part_idx hold ceil(V / 256) partials (256 rows a block).
+// logits float [V] (may be null, may be pinned host memory) = RMSNorm(h_last) .
+// W_lm^T (split layout as the embedding), then token (device or pinned host
+// memory) = argmax (lowest index on ties).
+// part_val/part_idx hold the blocks' partials: ceil(V / kLmMinRows) at most.
+constexpr int kLmMinRows = 32;
+// Rows per block for about `blocks` blocks: a multiple of kLmMinRows.
+int lm_head_rows(int vocab, int blocks);
 void launch_lm_head(const float* h_last, int d, float eps, const uint8_t* w_nib,
                     const uint16_t* w_scale, int vocab, float* logits, float* part_val,
-                    int32_t* part_idx, int32_t* token, hipStream_t s, int32_t* token2 = nullptr);
+                    int32_t* part_idx, int32_t* token, hipStream_t s);
 
 // Fill n 32-bit words with zero (graph-capturable, unlike memset nodes).
 void launch_zero(void* p, int64_t n_words, hipStream_t s);

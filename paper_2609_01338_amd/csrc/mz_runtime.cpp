@@ -460,10 +460,8 @@ struct mz_ctx {
   float* kvf = nullptr;    // [max_ctx][kv_pad]: key and value projections
   void* q16 = nullptr;     // f16 [max_ctx][dq]
   void* act = nullptr;     // f16 [max_ctx][ffp]
-  float* logits = nullptr;
   float* part_val = nullptr;
   int32_t* part_idx = nullptr;
-  int32_t* d_token = nullptr;
   int32_t* d_gen = nullptr;          // [max_ctx] tokens chosen by the steps of mz_generate
 
   // restore metadata: a pinned staging block and its device mirror of the
@@ -481,7 +479,9 @@ struct mz_ctx {
   int32_t* d_tok = nullptr;
   uint8_t* h_stage = nullptr;
   size_t stage_bytes = 0;
+  // pinned: the output head writes the first token and its logits here
   int32_t* h_token = nullptr;
+  float* h_logits = nullptr;
 
   // events
   std::vector<hipEvent_t> ev_w, ev_kv;
@@ -1322,11 +1322,9 @@ mz_status mz_load_model(const mz_model_cfg* cfg, const void* blob, size_t nbytes
     c.kvf = (float*)dmalloc((size_t)M * c.kv_pad * 4);
     c.q16 = dmalloc((size_t)M * c.dq * 2);
     c.act = dmalloc((size_t)M * c.ffp * 2);
-    c.logits = (float*)dmalloc((size_t)c.V * 4);
-    const int nblk = (c.V + 63) / 64;
+    const int nblk = (c.V + mzk::kLmMinRows - 1) / mzk::kLmMinRows;
     c.part_val = (float*)dmalloc((size_t)nblk * 4);
     c.part_idx = (int32_t*)dmalloc((size_t)nblk * 4);
-    c.d_token = (int32_t*)dmalloc(4);
     c.d_gen = (int32_t*)dmalloc((size_t)c.max_ctx * 4);
 
     // restore metadata
@@ -1353,6 +1351,10 @@ mz_status mz_load_model(const mz_model_cfg* cfg, const void* blob, size_t nbytes
     if (hipHostMalloc(&tokp, 64, hipHostMallocDefault) != hipSuccess || !tokp)
       fail(MZ_ENOMEM, "pinned allocation failed");
     c.h_token = (int32_t*)tokp;
+    void* lgp = nullptr;
+    if (hipHostMalloc(&lgp, (size_t)c.V * 4, hipHostMallocDefault) != hipSuccess || !lgp)
+      fail(MZ_ENOMEM, "pinned allocation failed");
+    c.h_logits = (float*)lgp;
     HIPCHK(hipDeviceSynchronize());
   });
   if (st != MZ_OK) {
@@ -1370,13 +1372,14 @@ void mz_free(mz_ctx* x) {
   if (x->s_swap) (void)hipStreamSynchronize(x->s_swap);
   void* dptrs[] = {x->codec_stage, x->d_meta, x->split_ws, x->attn_wq, x->gemm_wq, x->w_slab, x->emb_nib, x->emb_sc, x->lm_nib, x->lm_sc,
                    x->rope_cs, x->kv_slab,
-                   x->h[0], x->h[1], x->xb, x->qf, x->kvf, x->q16, x->act, x->logits, x->part_val,
-                   x->part_idx, x->d_token, x->d_gen};
+                   x->h[0], x->h[1], x->xb, x->qf, x->kvf, x->q16, x->act, x->part_val,
+                   x->part_idx, x->d_gen};
   for (void* p : dptrs)
     if (p) (void)hipFree(p);
   if (x->w_image) (void)hipHostFree(x->w_image);
   if (x->h_stage) (void)hipHostFree(x->h_stage);
   if (x->h_token) (void)hipHostFree(x->h_token);
+  if (x->h_logits) (void)hipHostFree(x->h_logits);
   x->arena.release_all();
   for (auto e : x->ev_w) if (e) (void)hipEventDestroy(e);
   for (auto e : x->ev_kv) if (e) (void)hipEventDestroy(e);
@@ -1676,13 +1679,11 @@ mz_status mz_first_token(mz_ctx* x, int32_t* token_out, float* logits_out) {
     if (!x->have_last) fail(MZ_ESTATE, "no prefill since the last first token");
     hipStream_t cs = x->s_compute;
     x->timed(kKLmHead, 2.0 * x->d * x->V, (double)x->V * x->d * 0.5625 + x->V * 4.0, cs, [&] {
-      mzk::launch_lm_head(x->h_last, x->d, x->cfg.rms_eps, x->lm_nib, x->lm_sc, x->V, x->logits,
-                          x->part_val, x->part_idx, x->d_token, cs);
+      mzk::launch_lm_head(x->h_last, x->d, x->cfg.rms_eps, x->lm_nib, x->lm_sc, x->V,
+                          logits_out ? x->h_logits : nullptr, x->part_val, x->part_idx, x->h_token, cs);
     });
-    HIPCHK(hipMemcpyAsync(x->h_token, x->d_token, 4, hipMemcpyDeviceToHost, cs));
-    if (logits_out)
-      HIPCHK(hipMemcpyAsync(logits_out, x->logits, (size_t)x->V * 4, hipMemcpyDeviceToHost, cs));
     HIPCHK(hipStreamSynchronize(cs));
+    if (logits_out) memcpy(logits_out, x->h_logits, (size_t)x->V * 4);
     *token_out = *x->h_token;
     x->have_last = false;
     if (x->swap_timed) {
@@ -1730,8 +1731,8 @@ mz_status mz_generate(mz_ctx* x, int32_t token, int32_t n, int32_t* tokens_out) 
         else
           restore_and_prefill_impl(x, &placeholder, 1, x->d_gen + (i - 1));
         x->timed(kKLmHead, 2.0 * x->d * x->V, (double)x->V * x->d * 0.5625 + x->V * 4.0, cs, [&] {
-          mzk::launch_lm_head(x->h_last, x->d, x->cfg.rms_eps, x->lm_nib, x->lm_sc, x->V, x->logits,
-                              x->part_val, x->part_idx, x->d_token, cs, x->d_gen + i);
+          mzk::launch_lm_head(x->h_last, x->d, x->cfg.rms_eps, x->lm_nib, x->lm_sc, x->V, nullptr,
+                              x->part_val, x->part_idx, x->d_gen + i, cs);
         });
         x->have_last = false;
         done = i + 1;

@@ -411,6 +411,41 @@ def test_scaled_8b_evict_size():
     _size_flow(w, [half // 2, half - half // 2, 10 ** 13], 56e9, 1e13, 2, prm, "8b-size", codec=True)
 
 
+@pytest.mark.parametrize("vocab", [31, 33, 1000, 70001, 300001])
+def test_output_head_vocab_sizes(vocab):
+    """The output head and its argmax against the oracle where the rows per
+    block change: fewer than one block's rows, a ragged last block, more than
+    32 rows a block, and more than 64 rows a wave (the logits are stored 64
+    rows at a time).  The first token without logits is the same token."""
+    import dataclasses
+    torch_cuda()
+    w = dataclasses.replace(TINY, model=dataclasses.replace(TINY.model, vocab=vocab)).scaled(n_ctx=32)
+    m = w.model
+    blob = W.make_blob(w)
+    ctx, _ = W.make_tokens(w)
+    hp = O.Hyper(m)
+    Kc, Vc, _ = O.clean_prefill(hp, O.Weights(hp, blob), ctx)
+    ox = O.OracleContext(m, blob)
+    ox.set_context(ctx)
+    C = m.chunk_tokens
+    with mz.Engine(m, blob, max_ctx=64) as eng:
+        mz.mz_set_context(eng.ctx, ctx)
+        for l in range(m.n_layers):
+            for c in range(w.n_chunks):
+                mz.mz_import_kv(eng.ctx, l, c, Kc[l][c * C:(c + 1) * C], Vc[l][c * C:(c + 1) * C])
+                ox.import_kv(l, c, Kc[l][c * C:(c + 1) * C], Vc[l][c * C:(c + 1) * C])
+        mz.mz_restore_and_prefill(eng.ctx, None)
+        tok, logits = mz.mz_first_token(eng.ctx, vocab)
+        mz.mz_restore_and_prefill(eng.ctx, None)
+        again = mz.mz_first_token(eng.ctx)
+    ox.restore_and_prefill(np.zeros(0, np.int32))
+    otok, ologits = ox.first_token()
+    err = float(np.abs(logits - ologits).max())
+    report("output head", vocab=vocab, token=tok, err=err)
+    assert err <= 5e-2
+    assert tok == otok == again == int(np.argmax(logits))
+
+
 @pytest.mark.parametrize("key,option", [
     ("8b", "fuse_norm"),
     pytest.param("8b", "gemv_qkv", marks=pytest.mark.skip(
