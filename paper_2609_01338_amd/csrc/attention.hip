@@ -908,6 +908,80 @@ __global__ __launch_bounds__(256) void attn_merge_wide_kernel(const _Float16* __
   }
 }
 
+// The same merge for many (row, head) pairs: HD / 8 lanes per pair, 8
+// dimensions each, 256 * 8 / HD pairs per workgroup, whose partials of a split
+// are one contiguous read.  The lanes of a pair load its (max, sum) entries
+// between them and share the weights by exchange; the outputs are summed in
+// split order with four splits' loads in flight.  Bound by reading the
+// partials: one workgroup per pair, reading 64 split slots each, took 145 us
+// for 59748 pairs x 3 splits of 128 dimensions (46 MB), this form 11.7 us for
+// 4 splits, and 15.2 -> 6.8 us for 4096 pairs.  Positions ascend, so the
+// workgroup's last row bounds its splits.
+template <int HD>
+__global__ __launch_bounds__(256) void attn_merge_rows_kernel(const _Float16* __restrict__ Opart,
+                                                              const float2* __restrict__ MLpart,
+                                                              const int32_t* __restrict__ qpos, int n_pairs, int nq,
+                                                              int n_split, int tps, _Float16* __restrict__ O) {
+  constexpr int LPE = HD / 8, EPB = 256 / LPE, R = 64 / LPE;
+  const int gl = threadIdx.x % LPE;
+  const int e0 = blockIdx.x * EPB, e = min(e0 + (int)threadIdx.x / LPE, n_pairs - 1);
+  const int nvb = min(n_split, (qpos[(min(e0 + EPB, n_pairs) - 1) / nq] / KT) / tps + 1);
+  const int nv = min(n_split, (qpos[e / nq] / KT) / tps + 1);
+  float2 ml[R];
+#pragma unroll
+  for (int k = 0; k < R; ++k) {
+    ml[k] = make_float2(-INFINITY, 0.f);
+    if (k * LPE < nvb) ml[k] = MLpart[(size_t)min(gl + k * LPE, nvb - 1) * n_pairs + e];
+  }
+  float mx = -INFINITY;
+#pragma unroll
+  for (int k = 0; k < R; ++k) {
+    if (!(gl + k * LPE < nv && ml[k].y > 0.f)) ml[k].x = -INFINITY;   // past the row's splits, or nothing seen
+    mx = fmaxf(mx, ml[k].x);
+  }
+#pragma unroll
+  for (int o = LPE / 2; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o));
+  float w[R], den = 0.f;
+#pragma unroll
+  for (int k = 0; k < R; ++k) {
+    w[k] = ml[k].x == -INFINITY ? 0.f : exp2f(ml[k].x - mx) * ml[k].y;
+    den += w[k];
+  }
+#pragma unroll
+  for (int o = LPE / 2; o > 0; o >>= 1) den += __shfl_xor(den, o);
+  float acc[8] = {};
+  const _Float16* p0 = Opart + (size_t)e * HD + gl * 8;
+  const size_t plane = (size_t)n_pairs * HD;
+#pragma unroll
+  for (int k = 0; k < R; ++k)
+#pragma unroll
+    for (int j = 0; j < LPE; j += 4) {
+      const int s0 = k * LPE + j;
+      if (s0 < nvb) {
+        f16x8 v[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) v[u] = *reinterpret_cast<const f16x8*>(p0 + (size_t)min(s0 + u, nvb - 1) * plane);
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          const float ws = __shfl(w[k], j + u, LPE);
+          if (ws > 0.f) {      // (an unwritten partial may hold anything)
+#pragma unroll
+            for (int d = 0; d < 8; ++d) acc[d] = __builtin_fmaf(ws, (float)v[u][d], acc[d]);
+          }
+        }
+      }
+    }
+  const float inv = 1.0f / den;
+  f16x8 o;
+#pragma unroll
+  for (int d = 0; d < 8; ++d) o[d] = (_Float16)(acc[d] * inv);
+  if (e0 + (int)threadIdx.x / LPE < n_pairs) *reinterpret_cast<f16x8*>(O + (size_t)e * HD + gl * 8) = o;
+}
+
+// Pairs from which the merge takes many pairs per workgroup; below, where
+// they would fill few CUs, one workgroup per pair.
+constexpr int kMergeRowsPairs = 2048;
+
 // The waves of a workgroup: gpw query heads of one KV head's group times qw
 // 32-row query groups, 8 waves in all: gpw is the largest divisor of the
 // group size G that divides 8 (G itself when it does), and a work item is a
@@ -1061,20 +1135,54 @@ int attention_auto_splits(int m, int max_pos, int n_q, int n_kv, int head_dim, i
   int gpw, qw;
   attn_wave_map(group, gpw, qw);
   const int n_qtiles = (m + 32 * qw - 1) / (32 * qw);
+  const bool few = m * group <= kFewCols;
   // workgroups per key split: one per KV head in the few-column kernel, one
   // per item and KV head in the tiled one
-  const int wgs = m * group <= kFewCols ? n_kv : n_qtiles * (group / gpw) * n_kv;
+  const int wgs = few ? n_kv : n_qtiles * (group / gpw) * n_kv;
   const int n_kt = max_pos / KT + 1;
-  // two workgroups per CU (their LDS fits twice) over 256 CUs -- one for
-  // the few-column kernel, which streams a split's keys fastest alone (8B
-  // decode step, 32900 keys: 30.5 us at 31 splits against 32.0 at 58, 36.7
-  // at 47 and 36.1 at 24) -- at least 4 key tiles per split, and partials
-  // that fit the workspace
-  constexpr int kTarget = 512, kMinTiles = 4, kMaxSplits = 64;
-  const int target = m * group <= kFewCols ? kTarget / 2 : kTarget;
-  if (wgs >= kTarget / 2 || n_kt < 2 * kMinTiles) return 1;
-  int ns = std::min({(target + wgs - 1) / wgs, n_kt / kMinTiles, kMaxSplits});
-  while (ns > 1 && attention_split_ws_bytes(m, n_q, head_dim, ns) > ws_cap) --ns;
+  // at least 4 key tiles per split, partials that fit the workspace
+  constexpr int kCus = 256, kMinTiles = 4, kMaxSplits = 64;
+  if (wgs >= kCus || n_kt < 2 * kMinTiles) return 1;
+  int cap = std::min(n_kt / kMinTiles, kMaxSplits);
+  while (cap > 1 && attention_split_ws_bytes(m, n_q, head_dim, cap) > ws_cap) --cap;
+  int ns = 1;
+  if (few) {
+    // one workgroup per CU: the few-column kernel streams a split's keys
+    // fastest alone (8B decode step, 32900 keys: 30.5 us at 31 splits against
+    // 32.0 at 58, 36.7 at 47 and 36.1 at 24)
+    ns = std::min((kCus + wgs - 1) / wgs, cap);
+  } else {
+    // One workgroup of the tiled kernel fits a CU (its registers; two per CU
+    // were aimed at before).  The smallest modelled time over the split
+    // counts, in key tiles of a workgroup: kStart of them pass before and
+    // after its key loop, and the partials are written and read at 5 TB/s.
+    // Rows that follow the context (a prompt) all see nearly every key: whole
+    // rounds of equal workgroups.  1024 and more, or half of the positions,
+    // are recomputed rows spread over the context, whose splits are on average
+    // half as many and even out.  128 rows at 32768 keys, 32/8 heads of 128:
+    // 16 splits 81 us, 31 92, 8 111; 4979 rows spread over 16384, 12/2 heads:
+    // 3 to 8 splits 300-327, 1 370.
+    constexpr double kStart = 6, kMerge = 3;       // tiles; us
+    const double tile_us = head_dim == 128 ? 1.9 : 1.0;
+    const bool spread = m >= 1024 || 2 * (int64_t)m >= (int64_t)max_pos + 1;
+    double best = 1e30;
+    for (int c = 1; c <= cap; ++c) {
+      const double len = (double)((n_kt + c - 1) / c) + kStart;
+      const double plane = 2.0 * m * n_q * head_dim * 2 / 5e6;   // us to write and read one split's partials
+      double us;
+      if (spread) {
+        us = std::max(wgs * (n_kt * 0.5 + kStart * (c + 1) * 0.5) / kCus + 0.5 * len, len) * tile_us;
+        if (c > 1) us += kMerge + plane * (c + 1) * 0.5;
+      } else {
+        us = (double)((wgs * c + kCus - 1) / kCus) * len * tile_us;
+        if (c > 1) us += kMerge + plane * c;
+      }
+      if (us < best) {
+        best = us;
+        ns = c;
+      }
+    }
+  }
   if (ns <= 1) return 1;
   const int tps = (n_kt + ns - 1) / ns;
   return (n_kt + tps - 1) / tps;   // no empty trailing split
@@ -1109,12 +1217,22 @@ void launch_attention_split(const void* q, const int32_t* qpos, int m, int max_p
     launch_any(q, qpos, m, slab, table, n_table, chunk_tokens, slot_bytes, n_q, n_kv, head_dim, out, sa, true, nullptr, s);
   }
   _Float16* O = reinterpret_cast<_Float16*>(out);
-  if (head_dim == 128)
-    hipLaunchKernelGGL(attn_merge_wide_kernel<128>, dim3(m * n_q), dim3(256), 0, s, sa.opart, sa.ml, qpos, m, n_q,
+  const int pairs = m * n_q;
+  if (pairs >= kMergeRowsPairs && (reinterpret_cast<uintptr_t>(out) & 15) == 0) {
+    const dim3 grid((unsigned)((pairs * (head_dim / 8) + 255) / 256));
+    if (head_dim == 128)
+      hipLaunchKernelGGL(attn_merge_rows_kernel<128>, grid, dim3(256), 0, s, sa.opart, sa.ml, qpos, pairs, n_q,
+                         sa.n_split, sa.tps, O);
+    else
+      hipLaunchKernelGGL(attn_merge_rows_kernel<64>, grid, dim3(256), 0, s, sa.opart, sa.ml, qpos, pairs, n_q,
+                         sa.n_split, sa.tps, O);
+  } else if (head_dim == 128) {
+    hipLaunchKernelGGL(attn_merge_wide_kernel<128>, dim3(pairs), dim3(256), 0, s, sa.opart, sa.ml, qpos, m, n_q,
                        sa.n_split, sa.tps, O);
-  else
-    hipLaunchKernelGGL(attn_merge_wide_kernel<64>, dim3(m * n_q), dim3(256), 0, s, sa.opart, sa.ml, qpos, m, n_q,
+  } else {
+    hipLaunchKernelGGL(attn_merge_wide_kernel<64>, dim3(pairs), dim3(256), 0, s, sa.opart, sa.ml, qpos, m, n_q,
                        sa.n_split, sa.tps, O);
+  }
 }
 
 }  // namespace mzk

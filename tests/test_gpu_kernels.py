@@ -705,6 +705,21 @@ def test_attention_split(nq, nkv, hd, C, S):
             _attn_case(nq, nkv, hd, C, S, qp, seed=20 + i, n_split=n_split)
 
 
+@pytest.mark.parametrize("nq,nkv,hd,C,S,m", [(6, 2, 128, 64, 1500, 343), (8, 2, 64, 64, 4200, 300),
+                                            (4, 4, 64, 16, 900, 513)])
+def test_attention_split_many_pairs(nq, nkv, hd, C, S, m):
+    """From 2048 (row, head) pairs on the merge takes 16 (head dimension 128)
+    or 32 pairs per workgroup: a ragged last workgroup, rows that see one
+    split next to rows that see all of them, and split counts at the edges of
+    a pair's lanes (8 and 16) and of its batches of 4."""
+    rng = np.random.default_rng(S)
+    rows = np.sort(rng.choice(S - 1, m - 2, replace=False) + 1)
+    qp = np.concatenate([[0], rows, [S - 1]])
+    sample = np.unique(np.concatenate([[0, 1, m - 2, m - 1], rng.integers(0, m, 60)]))
+    for n_split in (2, 7, 9, 14, 60):
+        _attn_case(nq, nkv, hd, C, S, qp, seed=n_split, sample=sample, n_split=n_split)
+
+
 @pytest.mark.parametrize("m", [1, 4, 129])
 def test_attention_split_8b_context(m):
     """The 8B layer at its full context (32768 cached + 128 prompt tokens):
