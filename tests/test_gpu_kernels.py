@@ -781,6 +781,42 @@ def test_kernel_entry_validation():
         mz.mz_attention_split(1, 1, 4, 10, 1, 1, 8193, 16, 8, 2, 64, 2, 1, 1 << 30, 1)
 
 
+def test_kv_codec_near_code_middles():
+    """Values whose quotient lies at or within one half-precision step of the
+    middle between two codes, where the kernel forms the correctly rounded
+    quotient itself, and groups with infinities: codes and parameters equal
+    the oracle's bit for bit.  Steps from subnormal to 2^6, three offsets."""
+    from oracle import kv_codec as Q
+    torch = torch_cuda()
+    rng = np.random.default_rng(3)
+    groups = []
+    for exp in range(-24, 7):
+        for mant in (1.0, 1.25, 1.0 + 2.0 ** -10, 2.0 - 2.0 ** -10, 1.0 + rng.random()):
+            d = float(np.float16(mant * 2.0 ** exp))
+            for off in (0.0, -100.0 * d, 3.0):
+                x = np.concatenate([[0.0, 255.0 * d], (rng.integers(0, 255, 62) + 0.5) * d]) + off
+                if np.abs(x).max() >= 65504:
+                    continue
+                h = x.astype(np.float16)
+                h[30:50] = (h[30:50].view(np.uint16) + rng.integers(0, 2, 20).astype(np.uint16)).view(np.float16)
+                groups.append(h)
+    inf = rng.standard_normal(64).astype(np.float16)
+    inf[5], inf[40] = np.inf, -2.0
+    groups.append(inf)
+    x = np.concatenate(groups)
+    n = x.size
+    with np.errstate(all="ignore"):
+        ref = Q.compress(x)
+    d_x = torch.from_numpy(x.view(np.int16)).cuda()
+    d_c = torch.empty(Q.compressed_bytes(n), dtype=torch.uint8, device="cuda")
+    mz.mz_kv_compress(d_x.data_ptr(), n, d_c.data_ptr(), stream())
+    torch.cuda.synchronize()
+    got = d_c.cpu().numpy()
+    assert np.array_equal(got[:n - 64], ref[:n - 64]), "codes"
+    assert np.array_equal(got[n:], ref[n:]), "group parameters"
+    assert not got[n - 64:n].any(), "a group of infinite range: every code 0"
+
+
 @pytest.mark.parametrize("n,scale_kind", [(64, "normal"), (4096, "normal"), (64 * 1237, "mixed"),
                                           (524288, "normal"), (640, "special")])
 def test_kv_codec_bit_exact(n, scale_kind):
