@@ -384,8 +384,9 @@ mz_status mz_q4_gemm(const void *x_f16, int32_t m, int32_t n_pad, int32_t k,
  * The output tiles are cut into 8 contiguous ranges, one per XCD; each
  * workgroup takes tiles of its XCD's range from a counter, then those left
  * in the other ranges, so XCDs that run at a higher clock take more of them.
- * Launches of fewer than 16 rounds of resident workgroups (4096 256-row
- * tiles on 256 compute units) run one workgroup per tile, as mz_q4_gemm.
+ * Products that run in other tiles than 256 x 256, and launches of fewer than
+ * 16 rounds of resident workgroups (4096 such tiles on 256 compute units),
+ * run one workgroup per tile, as mz_q4_gemm.
  * work_queues: device, caller-owned, 16 int32 that are zero before the first
  * call; each call leaves them zero.  Calls that share them must not be in
  * flight at the same time.  EINVAL as mz_q4_gemm, and for a NULL

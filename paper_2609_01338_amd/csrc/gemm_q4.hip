@@ -998,65 +998,67 @@ int gemm_splits(int k, int n_split) {
 
 // ---- which tiles, and how many K splits
 //
-// A product runs as 256 x 256 tiles (row_tile 256, this file) or as 32-, 64-
-// or 128-row tiles of 128 columns (gemm_rows.hip), each whole or split over K
-// (fp32 partials and a reduce).  The choice is the smallest of the modelled
-// times below: K steps of 64 per workgroup, times the time of a step at that
-// many resident workgroups, plus what the output and the partials move at 5
-// TB/s, plus fixed costs.  The 256-row tiles do the least dequantization and
-// LDS traffic per product and win where they fill whole rounds of the CUs
-// (8B gate/up, 8320 rows: 1685 us against 1837 as 128-row tiles); elsewhere
-// smaller tiles fill the chip (1.5B down projection, 4979 rows, 120 tiles of
-// 256 rows: 213 us before as 64-row tiles of 256 columns, 137 now as 128-row
-// tiles).  Step times measured on one MI355X with weights from HBM, in us:
-// row_tile 32: 0.34 with one workgroup per CU, 0.56 with two (64-row: 0.40,
-// 0.68; 128-row: 0.56, 0.97); 256-row: 1.42 on half of the CUs, 1.70 on all.
+// A product runs as 256 x 256 tiles (this file) or as 32 x 128, 64 x 128, 128
+// x 128 or 128 x 256 tiles (gemm_rows.hip), each whole or split over K (fp32
+// partials and a reduce).  The choice is the smallest of the modelled times
+// below: K steps of 64 per workgroup, times the time of a step at that many
+// resident workgroups, plus what the output and the partials move at 5 TB/s,
+// plus fixed costs.  The 256-row tiles do the least dequantization and LDS
+// traffic per product and win where they make whole rounds of the CUs (8B
+// output projection, 4096 rows: 118 us against 126 as 128 x 256 tiles);
+// elsewhere smaller tiles fill the chip (1.5B down projection, 4979 rows, 120
+// tiles of 256 rows: 213 us before as 64-row tiles of 256 columns, 137 now as
+// 128 x 128), and two workgroups per CU hide each other's start and end (1.5B
+// gate/up, 4979 rows: 255 us as 128 x 256, 284 as 256 x 256).
 struct GemmPlan {
-  int row_tile = 256, n_split = 1;
+  int row_tile = 256, col_tile = 256, n_split = 1;
   double us = 1e30;
 };
+
+// Step times measured on one MI355X with weights from HBM, in us: one
+// workgroup per CU (256-row: on half of the CUs), and the chip full (two per
+// CU; 256-row: one).  extra: steps' worth of start and end per round.
+struct TileTimes {
+  int row_tile, col_tile;
+  double t_lo, t_hi, extra;
+};
+constexpr TileTimes kTiles[] = {{256, 256, 1.40, 1.64, 4}, {128, 256, 1.10, 1.70, 1}, {128, 128, 0.56, 0.97, 1},
+                                {64, 128, 0.40, 0.68, 1},  {32, 128, 0.34, 0.56, 1}};
 
 // kSecondUs: the second workgroup of a CU starts behind the first
 constexpr double kLaunchUs = 3.0, kSecondUs = 1.0, kReduceUs = 3.2, kBytesPerUs = 5e6;
 constexpr int kMinSplitSteps = 4;
 
-double plan_us(int m, int n, int k, int row_tile, int ns) {
+double plan_us(int m, int n, int k, const TileTimes& t, int ns) {
   const double cus = device_cus();
-  const int bn = row_tile == 256 ? BN : 128;
-  const double w = (double)(n / bn) * ((m + row_tile - 1) / row_tile) * ns;
-  double t_lo, t_hi;   // a step at one workgroup per CU (256-row: on half of the CUs) and with the chip full
-  switch (row_tile) {
-    case 32: t_lo = 0.34, t_hi = 0.56; break;
-    case 64: t_lo = 0.40, t_hi = 0.68; break;
-    case 128: t_lo = 0.56, t_hi = 0.97; break;
-    default: t_lo = 1.42, t_hi = 1.70; break;
-  }
-  const double round = row_tile == 256 ? cus : 2 * cus;
+  const double w = (double)(n / t.col_tile) * ((m + t.row_tile - 1) / t.row_tile) * ns;
+  const double round = t.row_tile == 256 ? cus : 2 * cus;
   const double full = std::floor(w / round), rem = w - full * round;
-  double steps = full * t_hi;
-  if (rem > 0) steps += rem <= round / 2 ? t_lo : t_lo + (t_hi - t_lo) * (rem - round / 2) / (round / 2);
+  double steps = full * t.t_hi;
+  if (rem > 0) steps += rem <= round / 2 ? t.t_lo : t.t_lo + (t.t_hi - t.t_lo) * (rem - round / 2) / (round / 2);
   const double out = (double)ns * m * n * 4 / kBytesPerUs;
-  const double second = row_tile < 256 && w > cus ? kSecondUs : 0.;
-  return kLaunchUs + second + gemm_k_steps(k, ns) * steps + out + (ns > 1 ? kReduceUs + out : 0.);
+  const double second = t.row_tile < 256 && w > cus ? kSecondUs : 0.;
+  return kLaunchUs + second + (gemm_k_steps(k, ns) + t.extra - 1) * steps + out + (ns > 1 ? kReduceUs + out : 0.);
 }
 
 // The plan of a product of m rows with at most max_split splits whose
-// partials fit ws_cap bytes.  rows_ok: the smaller tiles may run.
+// partials fit ws_cap bytes.  rows_ok: the tiles of gemm_rows.hip may run.
 GemmPlan gemm_plan(int m, int n, int k, int64_t ws_cap, int max_split, bool rows_ok) {
   static const int kSplits[] = {1, 2, 3, 4, 6, 8, 12, 16, 24, 32};
   GemmPlan best;
   const int nk = k / BK;
-  // with many rounds of 256-row tiles nothing smaller pays
+  // with many rounds of 256-column tiles nothing smaller pays
   const bool many = (int64_t)(n / BN) * (m / BM) >= 4 * (int64_t)device_cus();
-  for (int row_tile : {256, 128, 64, 32}) {
-    if (row_tile < 256 && (!rows_ok || many)) break;
-    if (row_tile > 32 && row_tile < 256 && row_tile >= 2 * m) continue;
+  for (const TileTimes& t : kTiles) {
+    if (t.row_tile < 256 && !rows_ok) break;
+    if (many && t.col_tile < 256) break;
+    if (t.row_tile > 32 && t.row_tile < 256 && t.row_tile >= 2 * m) continue;
     for (int want : kSplits) {
-      if (want > max_split || (want > 1 && nk / want < kMinSplitSteps)) break;
+      if (want > max_split || (want > 1 && (many || nk / want < kMinSplitSteps))) break;
       const int ns = gemm_splits(k, want);
       if (ns > 1 && gemm_splitk_ws_bytes(m, n, ns) > ws_cap) break;
-      const double us = plan_us(m, n, k, row_tile, ns);
-      if (us < best.us) best = GemmPlan{row_tile, ns, us};
+      const double us = plan_us(m, n, k, t, ns);
+      if (us < best.us) best = GemmPlan{t.row_tile, t.col_tile, ns, us};
     }
   }
   return best;
@@ -1077,7 +1079,7 @@ bool gemm_rows_ok(int epilogue, const void* y, const GemmRope& ea) {
 
 // Splits of one product as partials in ws; returns how many were written.
 int launch_partials(const void* x, int m, int n, int k, const void* w, int n_split, void* ws, hipStream_t s,
-                    const int32_t* a_rows, const float* h_norm, float eps, int row_tile) {
+                    const int32_t* a_rows, const float* h_norm, float eps, const GemmPlan& plan) {
   const _Float16* X = reinterpret_cast<const _Float16*>(x);
   const uint8_t* W = reinterpret_cast<const uint8_t*>(w);
   const int ks = gemm_k_steps(k, n_split), ns = gemm_splits(k, n_split);
@@ -1087,10 +1089,10 @@ int launch_partials(const void* x, int m, int n, int k, const void* w, int n_spl
   else if (m == 1)
     hipLaunchKernelGGL(gemv_q4_kernel<false>, dim3(n / BN, ns), dim3(256), 0, s, X, nullptr, 0.f, a_rows, k, W,
                        n, reinterpret_cast<float*>(ws), ks);
-  else if (row_tile == 256)
+  else if (plan.row_tile == 256)
     launch_tiles<kEpiPartial>(X, a_rows, m, n, k, W, ws, s, ns, ks);
   else
-    launch_gemm_rows(x, a_rows, m, n, k, w, kEpiPartial, ws, s, row_tile, ns, ks);
+    launch_gemm_rows(x, a_rows, m, n, k, w, kEpiPartial, ws, s, plan.row_tile, plan.col_tile, ns, ks);
   return ns;
 }
 
@@ -1134,12 +1136,12 @@ void launch_planned(const GemmPlan& plan, const _Float16* X, const int32_t* a_ro
   else if (EPI == kEpiStore || EPI == kEpiAdd)
     yy = reinterpret_cast<float*>(y) + (size_t)r0 * n;
   if (plan.n_split > 1) {
-    const int ns = launch_partials(x, m, n, k, W, plan.n_split, ws, s, ar, nullptr, 0.f, plan.row_tile);
+    const int ns = launch_partials(x, m, n, k, W, plan.n_split, ws, s, ar, nullptr, 0.f, plan);
     launch_reduce(reinterpret_cast<const float*>(ws), ns, m, n, EPI, e, yy, s);
   } else if (plan.row_tile == 256) {
     launch_tiles<EPI>(x, ar, m, n, k, W, yy, s, 1, 0, e, wq);
   } else {
-    launch_gemm_rows(x, ar, m, n, k, W, EPI, yy, s, plan.row_tile, 1, 0, e);
+    launch_gemm_rows(x, ar, m, n, k, W, EPI, yy, s, plan.row_tile, plan.col_tile, 1, 0, e);
   }
 }
 
@@ -1157,7 +1159,7 @@ void launch_epi(const _Float16* X, const int32_t* a_rows, int m, int n, int k, c
   const int full = m / BM * BM, rem = m - full;
   if (rem > 0 && full > 0) {
     const GemmPlan tail = gemm_plan(rem, n, k, ws_bytes, ns_cap, ok);
-    if (plan_us(full, n, k, 256, 1) + tail.us < whole.us) {
+    if (plan_us(full, n, k, kTiles[0], 1) + tail.us < whole.us) {
       launch_planned<EPI>(GemmPlan{}, X, a_rows, 0, full, n, k, W, y, s, ea, wq, ws);
       launch_planned<EPI>(tail, X, a_rows, full, rem, n, k, W, y, s, ea, nullptr, ws);
       return;
@@ -1259,7 +1261,7 @@ template <int EPI>
 void launch_splitk(const void* x, int m, int n, int k, const void* w, const GemmRope& ea, void* y, int n_split,
                    void* ws, hipStream_t s, const int32_t* a_rows, const float* h_norm, float eps) {
   if (m == 1) {   // the split GEMV
-    const int ns = launch_partials(x, m, n, k, w, n_split, ws, s, a_rows, h_norm, eps, 0);
+    const int ns = launch_partials(x, m, n, k, w, n_split, ws, s, a_rows, h_norm, eps, GemmPlan{});
     launch_reduce(reinterpret_cast<const float*>(ws), ns, m, n, EPI, ea, y, s);
     return;
   }

@@ -322,16 +322,19 @@ def test_gemm_restore_launches(key):
                 assert np.abs(a1 - a2).max() <= 4 * F16_REL * scale, (key, rows_name, epi)
 
 
-@pytest.mark.parametrize("epi,hd", [(0, 0), (1, 0), (2, 0), (4, 32), (4, 64), (4, 128), (5, 32), (5, 64), (5, 128)])
-def test_gemm_tile_heights_same_bits(epi, hd):
+@pytest.mark.parametrize("epi,hd,K", [
+    (0, 0, 192), (1, 0, 192), (2, 0, 192), (4, 32, 192), (4, 64, 192), (4, 128, 192), (5, 32, 192), (5, 64, 192),
+    (5, 128, 192), (1, 0, 5440), (2, 0, 5440), (4, 128, 5440), (5, 64, 5440)])
+def test_gemm_tile_shapes_same_bits(epi, hd, K):
     """A product's first rows by themselves -- so few that they run as 32-, 64-
-    or 128-row tiles -- against the same rows of a product that fills the
-    chip with 256-row tiles: bit for bit, with every epilogue, an odd number
-    of 64-wide K steps, row counts at the edges of every tile height, a row
-    list, and (keys and values) rows that write nothing and positions that
-    do not start on a slot."""
+    or 128-row tiles of 128 columns -- against the same rows of a product
+    that fills the chip with 128 x 256 tiles (K 192) or with four whole rounds
+    of 256 x 256 tiles (K 5440): bit for bit, with every epilogue, an odd
+    number of 64-wide K steps, row counts at the edges of every tile height,
+    a row list, and (keys and values) rows that write nothing and positions
+    that do not start on a slot."""
     torch = torch_cuda()
-    M, N, K, C = 4096, 16384, 192, 16
+    M, N, C = 4096, 16384, 16
     gen = torch.Generator(device="cuda").manual_seed(epi * 10 + hd)
     X = torch.randn(M, K, device="cuda", generator=gen).to(torch.float16)
     W_ = torch.randint(0, 256, (N // 256, K // 64, 9216), device="cuda", dtype=torch.uint8, generator=gen)
