@@ -11,8 +11,8 @@
 // ([dkv][C], "hidden-dimension-first"), so both tiles load as plain 16-byte
 // rows.  A workgroup serves one KV head and a tile of query rows for all of
 // that head's G query heads when G divides 8 (8 waves: G heads x 8/G groups of
-// 32 rows), else for one of them (8 waves of 32 rows); each wave owns 32
-// queries of one query head.  Per 64-key tile K and V^T are staged in LDS
+// 32 rows), else for some of them (attn_wave_map), or the same with 4 waves
+// (attn_four_waves); each wave owns 32 queries of one query head.  Per 64-key tile K and V^T are staged in LDS
 // once for the whole workgroup, double
 // buffered: the next tile's global loads are in flight while the current one
 // is multiplied.  Scores are computed transposed, S^T = K Q^T,
@@ -568,7 +568,7 @@ __device__ __forceinline__ int attn_pop(int* wq, int home, int nkv, int n_items)
 // XCDs run at different clocks under the power limit, and with a fixed share
 // each the slowest one sets the end of the launch.
 template <int HD, int NW, bool DIRECT, bool SPLIT>
-__global__ __launch_bounds__(64 * NW) void attn_kernel(const _Float16* __restrict__ Q,
+__global__ __launch_bounds__(64 * NW, 2) void attn_kernel(const _Float16* __restrict__ Q,
                                                        const int32_t* __restrict__ qpos, int M,
                                                        const uint8_t* __restrict__ slab,
                                                        const int32_t* __restrict__ table, int n_table, int C,
@@ -1002,6 +1002,27 @@ inline void attn_wave_map(int group, int& gpw, int& qw) {
   qw = 8 / gpw;
 }
 
+// Whether a launch takes workgroups of four waves (half the rows, two
+// workgroups per CU) instead of eight.  Each staged key tile then serves half
+// the queries, which costs 26 % where the chip is full of items; but a launch
+// of few items lasts as long as its heaviest, and two half-size ones on a CU
+// even out: up to one and a half rounds of the CUs (an item is 256 (row, head)
+// pairs), and every key split.  Same bits.  On one MI355X, us, eight against
+// four waves: 2048 causal rows, 32/8 heads of 64 (256 items) 41.0 and 34.9;
+// 2048 rows, 12/2 heads of 128 (96 items) 55.3 and 41.3; 3072 rows, 32/8 of
+// 128 (384) 94.3 and 92.4, 4096 (512) 146.6 and 149.6; 17 rows at 32768 keys
+// in 31 splits 41.7 and 32.5 (half of an eight-wave tile would be empty), 4979
+// rows at 16384 in 4 splits 332 and 309.  Chunks shorter than a key tile come
+// through registers, which four waves have fewer of per row: with heads of 128
+// eight waves stay (17 rows, 31 splits 63 against 75), with 64 the line is at
+// half a round (1024 rows 28.0 and 27.0, 2048 49.9 and 50.6).
+inline bool attn_four_waves(int m, int n_q, int group, int head_dim, int chunk_tokens, bool split) {
+  if (group >= 8) return false;
+  const int64_t pairs = (int64_t)m * n_q;
+  if (chunk_tokens >= KT) return split || pairs <= 384 * 256;
+  return head_dim == 64 && (split || pairs <= 128 * 256);
+}
+
 struct SplitArgs {
   int tps = 0, n_split = 1;
   _Float16* opart = nullptr;
@@ -1083,9 +1104,7 @@ void launch_hd(const _Float16* Q, const int32_t* qpos, int m, const uint8_t* S, 
                int C, int cshift, int64_t slot_bytes, int nq, int nkv, int group, int qw, int gpw, int n_table,
                float scale_log2, _Float16* O, const SplitArgs& sa, int* wq, hipStream_t s) {
   switch (gpw * qw) {
-    case 5: launch_nw<HD, 5, SPLIT>(Q, qpos, m, S, table, C, cshift, slot_bytes, nq, nkv, group, qw, gpw, n_table, scale_log2, O, sa, wq, s); break;
-    case 6: launch_nw<HD, 6, SPLIT>(Q, qpos, m, S, table, C, cshift, slot_bytes, nq, nkv, group, qw, gpw, n_table, scale_log2, O, sa, wq, s); break;
-    case 7: launch_nw<HD, 7, SPLIT>(Q, qpos, m, S, table, C, cshift, slot_bytes, nq, nkv, group, qw, gpw, n_table, scale_log2, O, sa, wq, s); break;
+    case 4: launch_nw<HD, 4, SPLIT>(Q, qpos, m, S, table, C, cshift, slot_bytes, nq, nkv, group, qw, gpw, n_table, scale_log2, O, sa, wq, s); break;
     default: launch_nw<HD, 8, SPLIT>(Q, qpos, m, S, table, C, cshift, slot_bytes, nq, nkv, group, qw, gpw, n_table, scale_log2, O, sa, wq, s); break;
   }
 }
@@ -1096,6 +1115,10 @@ void launch_any(const void* q, const int32_t* qpos, int m, const void* slab, con
   const int group = n_q / n_kv;          // 1..8
   int gpw, qw;
   attn_wave_map(group, gpw, qw);
+  if (attn_four_waves(m, n_q, group, head_dim, chunk_tokens, split)) {
+    gpw = group % 4 == 0 ? 4 : group % 2 == 0 ? 2 : 1;
+    qw = 4 / gpw;
+  }
   const float scale_log2 = 1.4426950408889634f / __builtin_sqrtf((float)head_dim);
   const _Float16* Q = reinterpret_cast<const _Float16*>(q);
   const uint8_t* S = reinterpret_cast<const uint8_t*>(slab);
@@ -1152,8 +1175,8 @@ int attention_auto_splits(int m, int max_pos, int n_q, int n_kv, int head_dim, i
     // 32.0 at 58, 36.7 at 47 and 36.1 at 24)
     ns = std::min((kCus + wgs - 1) / wgs, cap);
   } else {
-    // One workgroup of the tiled kernel fits a CU (its registers; two per CU
-    // were aimed at before).  The smallest modelled time over the split
+    // One eight-wave workgroup of the tiled kernel, or two of four waves,
+    // fit a CU (its registers).  The smallest modelled time over the split
     // counts, in key tiles of a workgroup: kStart of them pass before and
     // after its key loop, and the partials are written and read at 5 TB/s.
     // Rows that follow the context (a prompt) all see nearly every key: whole
@@ -1161,8 +1184,11 @@ int attention_auto_splits(int m, int max_pos, int n_q, int n_kv, int head_dim, i
     // are recomputed rows spread over the context, whose splits are on average
     // half as many and even out.  128 rows at 32768 keys, 32/8 heads of 128:
     // 16 splits 81 us, 31 92, 8 111; 4979 rows spread over 16384, 12/2 heads:
-    // 3 to 8 splits 300-327, 1 370.
-    constexpr double kStart = 6, kMerge = 3;       // tiles; us
+    // 2 to 8 splits 295-315, 1 348.
+    // Unsplit, four-wave workgroups even out two to a CU: kWhole of the time
+    // (1024 rows, 24/8 heads of 128: unsplit 24.8 us, 2 splits 27.0; 2048 rows
+    // 49.2 and 50.4; 2048 rows of 12/2 heads 40.6 and 34.1 in 3 splits).
+    constexpr double kStart = 6, kMerge = 3, kWhole = 0.8;   // tiles; us; 1
     const double tile_us = head_dim == 128 ? 1.9 : 1.0;
     const bool spread = m >= 1024 || 2 * (int64_t)m >= (int64_t)max_pos + 1;
     double best = 1e30;
@@ -1172,7 +1198,10 @@ int attention_auto_splits(int m, int max_pos, int n_q, int n_kv, int head_dim, i
       double us;
       if (spread) {
         us = std::max(wgs * (n_kt * 0.5 + kStart * (c + 1) * 0.5) / kCus + 0.5 * len, len) * tile_us;
-        if (c > 1) us += kMerge + plane * (c + 1) * 0.5;
+        if (c > 1)
+          us += kMerge + plane * (c + 1) * 0.5;
+        else
+          us *= kWhole;
       } else {
         us = (double)((wgs * c + kCus - 1) / kCus) * len * tile_us;
         if (c > 1) us += kMerge + plane * c;

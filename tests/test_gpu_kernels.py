@@ -723,6 +723,19 @@ def test_attention_split_many_pairs(nq, nkv, hd, C, S, m):
         _attn_case(nq, nkv, hd, C, S, qp, seed=n_split, sample=sample, n_split=n_split)
 
 
+@pytest.mark.parametrize("nq,nkv,hd,C,line", [(32, 8, 128, 64, 3072), (24, 8, 128, 256, 4096), (48, 8, 64, 64, 2048),
+                                              (32, 8, 64, 16, 1024), (40, 8, 128, 128, 2457)])
+def test_attention_wave_count_line(nq, nkv, hd, C, line):
+    """Up to `line` rows an unsplit launch takes workgroups of four waves,
+    above it of eight (groups 4, 3, 6, 4 and 5): first and last rows, tile
+    edges of both and a ragged last tile, with and without the work queues."""
+    rng = np.random.default_rng(line)
+    for m in (line - 3, line, line + 1):
+        sample = np.unique(np.concatenate([[0, 31, 32, 63, 64, 127, 128, m - 130, m - 2, m - 1], rng.integers(0, m, 30)]))
+        _attn_case(nq, nkv, hd, C, m + 40, np.arange(40, m + 40), seed=m, sample=sample,
+                   n_split="queued" if m != line else None)
+
+
 @pytest.mark.parametrize("m", [1, 4, 129])
 def test_attention_split_8b_context(m):
     """The 8B layer at its full context (32768 cached + 128 prompt tokens):
