@@ -1002,6 +1002,17 @@ inline void attn_wave_map(int group, int& gpw, int& qw) {
   qw = 8 / gpw;
 }
 
+// Dynamic LDS of a launch: the K/V tiles, double buffered, the item of the
+// persistent form and, with direct loads, the copy of the chunk table.
+template <int HD, bool DIRECT>
+constexpr size_t attn_lds_bytes(int n_table) {
+  return 2 * (k_tile_halves<HD>() + v_tile_halves<HD>()) * sizeof(_Float16) + 16 +
+         (DIRECT ? 4 * (size_t)((n_table + 3) & ~3) : 0);
+}
+
+// Query heads of a group that a workgroup of four waves takes.
+inline int attn_four_heads(int group) { return group % 4 == 0 ? 4 : group % 2 == 0 ? 2 : 1; }
+
 // Whether a launch takes workgroups of four waves (half the rows, two
 // workgroups per CU) instead of eight.  Each staged key tile then serves half
 // the queries, which costs 26 % where the chip is full of items; but a launch
@@ -1016,10 +1027,22 @@ inline void attn_wave_map(int group, int& gpw, int& qw) {
 // through registers, which four waves have fewer of per row: with heads of 128
 // eight waves stay (17 rows, 31 splits 63 against 75), with 64 the line is at
 // half a round (1024 rows 28.0 and 27.0, 2048 49.9 and 50.6).
-inline bool attn_four_waves(int m, int n_q, int group, int head_dim, int chunk_tokens, bool split) {
+inline bool attn_four_waves(int m, int n_q, int group, int head_dim, int chunk_tokens, int n_table, bool split,
+                            int n_split) {
   if (group >= 8) return false;
   const int64_t pairs = (int64_t)m * n_q;
-  if (chunk_tokens >= KT) return split || pairs <= 384 * 256;
+  if (chunk_tokens >= KT) {
+    // two workgroups of heads of 128 fit a CU's LDS with tables of up to 4092
+    // entries; past that four waves pay only while each has a CU to itself (8192
+    // entries, 32/8 heads: 17 rows in 31 splits 33.7 us against 44.7 with eight,
+    // 1024 causal rows 25.2 against 32.2, but 128 rows in 16 splits 98.2 against
+    // 82.0)
+    if (head_dim == 128 && 2 * attn_lds_bytes<128, true>(n_table) > 160 * 1024) {
+      const int gpw = attn_four_heads(group), rows = 32 * (4 / gpw);
+      if ((int64_t)((m + rows - 1) / rows) * (n_q / gpw) * n_split > 256) return false;
+    }
+    return split || pairs <= 384 * 256;
+  }
   return head_dim == 64 && (split || pairs <= 128 * 256);
 }
 
@@ -1048,14 +1071,6 @@ int resident_wgs(size_t lds_bytes) {
     per = 1;
   cache[lds_bytes] = cus * per;
   return cus * per;
-}
-
-// Dynamic LDS of a launch: the K/V tiles, double buffered, the item of the
-// persistent form and, with direct loads, the copy of the chunk table.
-template <int HD, bool DIRECT>
-constexpr size_t attn_lds_bytes(int n_table) {
-  return 2 * (k_tile_halves<HD>() + v_tile_halves<HD>()) * sizeof(_Float16) + 16 +
-         (DIRECT ? 4 * (size_t)((n_table + 3) & ~3) : 0);
 }
 
 template <int HD, int NW, bool DIRECT, bool SPLIT>
@@ -1115,8 +1130,8 @@ void launch_any(const void* q, const int32_t* qpos, int m, const void* slab, con
   const int group = n_q / n_kv;          // 1..8
   int gpw, qw;
   attn_wave_map(group, gpw, qw);
-  if (attn_four_waves(m, n_q, group, head_dim, chunk_tokens, split)) {
-    gpw = group % 4 == 0 ? 4 : group % 2 == 0 ? 2 : 1;
+  if (attn_four_waves(m, n_q, group, head_dim, chunk_tokens, n_table, split, sa.n_split)) {
+    gpw = attn_four_heads(group);
     qw = 4 / gpw;
   }
   const float scale_log2 = 1.4426950408889634f / __builtin_sqrtf((float)head_dim);
