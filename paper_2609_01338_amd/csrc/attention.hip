@@ -944,8 +944,10 @@ __global__ __launch_bounds__(256) void attn_merge_rows_kernel(const _Float16* __
   float w[R], den = 0.f;
 #pragma unroll
   for (int k = 0; k < R; ++k) {
-    w[k] = ml[k].x == -INFINITY ? 0.f : exp2f(ml[k].x - mx) * ml[k].y;
-    den += w[k];
+    // -1: not used.  A weight that underflows to 0 is used all the same, so an
+    // infinite or NaN partial shows as it does in the other forms.
+    w[k] = ml[k].x == -INFINITY ? -1.f : exp2f(ml[k].x - mx) * ml[k].y;
+    if (!(w[k] < 0.f)) den += w[k];
   }
 #pragma unroll
   for (int o = LPE / 2; o > 0; o >>= 1) den += __shfl_xor(den, o);
@@ -964,7 +966,7 @@ __global__ __launch_bounds__(256) void attn_merge_rows_kernel(const _Float16* __
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
           const float ws = __shfl(w[k], j + u, LPE);
-          if (ws > 0.f) {      // (an unwritten partial may hold anything)
+          if (!(ws < 0.f)) {   // (an unwritten partial may hold anything)
 #pragma unroll
             for (int d = 0; d < 8; ++d) acc[d] = __builtin_fmaf(ws, (float)v[u][d], acc[d]);
           }

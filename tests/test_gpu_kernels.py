@@ -723,6 +723,44 @@ def test_attention_split_many_pairs(nq, nkv, hd, C, S, m):
         _attn_case(nq, nkv, hd, C, S, qp, seed=n_split, sample=sample, n_split=n_split)
 
 
+@pytest.mark.parametrize("m", [100, 400])
+def test_attention_split_nonfinite_values(m):
+    """An infinite and a NaN value under keys whose weight underflows to 0 (the
+    score lies 369 powers of two below the others): the value's dimension is
+    not finite in the plain form, where 0 * inf is NaN, and so it has to be in
+    either merge (400 rows of 8 heads: many pairs per workgroup; 100: one
+    each); every other dimension is the plain form's to the f16 rounding of
+    the partials."""
+    torch = torch_cuda()
+    nq, nkv, hd, C, S, n_split = 8, 2, 64, 64, 1024, 8
+    n = S // C
+    gen = torch.Generator(device="cuda").manual_seed(m)
+    K = torch.full((n, C, nkv * hd), 4.0, device="cuda")
+    K[:2] = -4.0                                         # the first split: keys 0..127
+    V = torch.randn(n, nkv * hd, C, device="cuda", generator=gen)
+    V[0, 3, 5], V[1, 17, 9] = float("inf"), float("nan")   # both of KV head 0
+    slab = torch.cat([K.reshape(n, -1), V.reshape(n, -1)], 1).half()
+    table = torch.arange(n, device="cuda", dtype=torch.int32)
+    q = torch.full((m, nq * hd), 4.0, device="cuda", dtype=torch.float16)
+    pos = torch.arange(S - m, S, device="cuda", dtype=torch.int32)
+    args = (slab.data_ptr(), table.data_ptr(), n, C, nq, nkv, hd)
+    plain, split = torch.zeros_like(q), torch.zeros_like(q)
+    mz.mz_attention(q.data_ptr(), pos.data_ptr(), m, *args, plain.data_ptr(), stream())
+    wsb = mz.mz_attention_split_workspace_bytes(m, nq, hd, n_split)
+    ws = torch.empty(wsb, device="cuda", dtype=torch.uint8)
+    mz.mz_attention_split(q.data_ptr(), pos.data_ptr(), m, S - 1, *args, n_split, ws.data_ptr(), wsb,
+                          split.data_ptr(), stream())
+    torch.cuda.synchronize()
+    bad = torch.zeros(m, nq, hd, dtype=torch.bool, device="cuda")
+    bad[:, :nq // nkv, [3, 17]] = True
+    assert torch.equal(~torch.isfinite(plain.view(m, nq, hd)), bad)
+    assert torch.equal(~torch.isfinite(split.view(m, nq, hd)), bad)
+    ok = ~bad.view(m, -1)
+    vmax = float(V[torch.isfinite(V)].abs().max())       # partials and results are convex combinations of values
+    # each form lies within 2^-10 vmax of the exact rows, the split one 2^-11 more for its partials, and outputs round to f16
+    assert float((split - plain)[ok].abs().max()) <= 3 * 2.0 ** -10 * vmax
+
+
 @pytest.mark.parametrize("nq,nkv,hd,C,line", [(32, 8, 128, 64, 3072), (24, 8, 128, 256, 4096), (48, 8, 64, 64, 2048),
                                               (32, 8, 64, 16, 1024), (40, 8, 128, 128, 2457)])
 def test_attention_wave_count_line(nq, nkv, hd, C, line):
