@@ -607,7 +607,7 @@ __global__ __launch_bounds__(256) void gemm_splitk_reduce(const float* __restric
     for (int e = 0; e < 4; ++e) y[e] = (_Float16)(silu(g[e]) * u[e]);
   } else {
     const float* pp = part + (size_t)row * N + o;
-    f32x4* y = reinterpret_cast<f32x4*>(reinterpret_cast<float*>(Y) + (size_t)row * N + o);
+    f32x4_out* y = reinterpret_cast<f32x4_out*>(reinterpret_cast<float*>(Y) + (size_t)row * N + o);
     f32x4 c = {};
     if (EPI == kEpiAdd) c = *y;
     const f32x4 a = split_sum<f32x4>(pp, ns, plane);
@@ -1064,18 +1064,10 @@ GemmPlan gemm_plan(int m, int n, int k, int64_t ws_cap, int max_split, bool rows
   return best;
 }
 
-// What the vector stores of the small tiles need of the output: 16-byte
-// alignment (fp32) or 8-byte (f16), whole heads of rotated columns, and slots
-// and queries off the 4-column groups' way.
-bool gemm_rows_ok(int epilogue, const void* y, const GemmRope& ea) {
-  const uintptr_t a = reinterpret_cast<uintptr_t>(y);
-  switch (epilogue) {
-    case kEpiSwiGLU: return (a & 7) == 0;
-    case kEpiRopeQ: return (a & 7) == 0 && ea.n_valid % ea.hd == 0;
-    case kEpiRopeKV: return ea.n_valid % (2 * ea.hd) == 0;
-    default: return (a & 15) == 0;
-  }
-}
+// The small tiles take codes and scales by LDS-DMA, from 16-byte pieces;
+// weights that start elsewhere run as 256-row tiles, which read them into
+// registers.
+bool gemm_rows_ok(const void* w) { return (reinterpret_cast<uintptr_t>(w) & 15) == 0; }
 
 // Splits of one product as partials in ws; returns how many were written.
 int launch_partials(const void* x, int m, int n, int k, const void* w, int n_split, void* ws, hipStream_t s,
@@ -1149,8 +1141,8 @@ template <int EPI>
 void launch_epi(const _Float16* X, const int32_t* a_rows, int m, int n, int k, const uint8_t* W, void* y,
                 hipStream_t s, const GemmRope& ea = GemmRope{}, int* wq = nullptr, void* ws = nullptr,
                 int64_t ws_bytes = 0, int max_split = 32) {
-  const bool ok = gemm_rows_ok(EPI, y, ea);
-  const int ns_cap = ws && ok ? max_split : 1;
+  const bool ok = gemm_rows_ok(W);
+  const int ns_cap = ws ? max_split : 1;
   const GemmPlan whole = gemm_plan(m, n, k, ws_bytes, ns_cap, ok);
   // A ragged last row of 256-row tiles can make a final round of workgroups
   // that occupies few CUs (16 column tiles x 129 row tiles = 8 rounds + 16

@@ -288,7 +288,7 @@ __global__ __launch_bounds__(NT, 2) void gemm_rows_kernel(
         f16x4 o;
 #pragma unroll
         for (int e = 0; e < 4; ++e) o[e] = swiglu_f16(acc[i][t][e], acc[i][t + 1][e]);
-        *reinterpret_cast<f16x4*>(reinterpret_cast<_Float16*>(Y) + (size_t)row * (N / 2) + ct / 2 + 4 * g) = o;
+        *reinterpret_cast<f16x4_out*>(reinterpret_cast<_Float16*>(Y) + (size_t)row * (N / 2) + ct / 2 + 4 * g) = o;
       } else if constexpr (ROPE) {
         const int rot = EPI == kEpiRopeQ ? ea.n_valid : ea.n_valid >> 1;   // rotated columns
         if (ct < rot) {
@@ -303,16 +303,8 @@ __global__ __launch_bounds__(NT, 2) void gemm_rows_kernel(
             o1[e] = (_Float16)q.x;
             o2[e] = (_Float16)q.y;
           }
-          if (EPI == kEpiRopeQ || (reinterpret_cast<uintptr_t>(y) & 7) == 0) {
-            *reinterpret_cast<f16x4*>(y + c0) = o1;
-            *reinterpret_cast<f16x4*>(y + c0 + half) = o2;
-          } else {                                       // a key row off an 8-byte boundary
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-              y[c0 + e] = o1[e];
-              y[c0 + half + e] = o2[e];
-            }
-          }
+          *reinterpret_cast<f16x4_out*>(y + c0) = o1;
+          *reinterpret_cast<f16x4_out*>(y + c0 + half) = o2;
         } else if (EPI == kEpiRopeKV) {
           // values: V^T[c][pos % C]; the 16 lanes of a row group are 16
           // activation rows, neighbouring positions in most launches
@@ -331,7 +323,7 @@ __global__ __launch_bounds__(NT, 2) void gemm_rows_kernel(
         float* y = reinterpret_cast<float*>(Y) + ((size_t)split * M + row) * N + c0;
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
-          f32x4* d = reinterpret_cast<f32x4*>(y + 16 * h);
+          f32x4_out* d = reinterpret_cast<f32x4_out*>(y + 16 * h);
           *d = EPI == kEpiAdd ? *d + acc[i][t + h] : acc[i][t + h];
         }
       }

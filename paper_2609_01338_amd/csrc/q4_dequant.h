@@ -10,6 +10,9 @@ typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 typedef _Float16 f16x4 __attribute__((ext_vector_type(4)));
 typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+// four values of a caller's output, which may start at any element
+typedef f32x4 f32x4_out __attribute__((aligned(4)));
+typedef f16x4 f16x4_out __attribute__((aligned(2)));
 typedef __attribute__((address_space(3))) void lds_void;
 
 __device__ __forceinline__ float silu(float g) { return g / (1.0f + __expf(-g)); }

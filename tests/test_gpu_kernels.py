@@ -376,6 +376,72 @@ def test_gemm_tile_shapes_same_bits(epi, hd, K):
             assert not bool((a[~mask] != 0).any()), (m, half)      # nothing else was written
 
 
+def _byte_view(t, shift):
+    """A copy of t that starts `shift` bytes after a 256-byte boundary, and
+    the buffer around it (0x55 bytes elsewhere)."""
+    torch = torch_cuda()
+    raw = t.reshape(-1).view(torch.uint8)
+    buf = torch.full((raw.numel() + 512,), 0x55, device="cuda", dtype=torch.uint8)
+    buf[256 + shift:256 + shift + raw.numel()] = raw
+    return buf, buf.data_ptr() + 256 + shift
+
+
+@pytest.mark.parametrize("m", [17, 200])
+@pytest.mark.parametrize("epi,hd", [(0, 0), (1, 0), (2, 0), (4, 64), (5, 128)])
+def test_gemm_unaligned_operands(m, epi, hd):
+    """Outputs that start at any element take the same tiles and K splits as
+    aligned ones: the same bits, nothing written beside them.  Weights off a
+    16-byte boundary run as 256-row tiles: without a workspace the same bits,
+    with one the K splits may be others (fp32 sums in another order)."""
+    torch = torch_cuda()
+    K, N, C = 2048, 1024, 16
+    gen = torch.Generator(device="cuda").manual_seed(epi)
+    X = torch.randn(m, K, device="cuda", generator=gen).half()
+    W_ = torch.randint(0, 256, (N // 256, K // 64, 9216), device="cuda", dtype=torch.uint8, generator=gen)
+    sc = (torch.rand(N // 256, K // 64, 512, device="cuda", generator=gen) * 0.01 + 0.01).half()
+    W_[..., 8192:] = sc.view(torch.uint8).view(N // 256, K // 64, 1024)
+    pos = torch.arange(5, 5 + m, device="cuda", dtype=torch.int32)
+    slot = C * (N // 2) * 4
+    off = (pos.long() // C) * slot + (pos.long() % C) * N
+    cs = torch.randn(m + 5, max(hd // 2, 1), 2, device="cuda", generator=gen)
+    if epi < 2:
+        y0 = torch.randn(m, N, device="cuda", generator=gen)
+    elif epi == 5:
+        y0 = torch.zeros((m + 5 + C) // C * slot // 2, device="cuda", dtype=torch.float16)
+    else:
+        y0 = torch.zeros(m, N // 2 if epi == 2 else N, device="cuda", dtype=torch.float16)
+    wsb = 64 << 20
+
+    def run(y_shift, w_shift, split):
+        buf, yp = _byte_view(y0, y_shift)
+        wbuf, wp = _byte_view(W_, w_shift)
+        ws = torch.full((wsb // 4,), float("nan"), device="cuda")
+        kw = dict(workspace=ws.data_ptr(), workspace_bytes=wsb) if split else {}
+        report("unaligned", epi=epi, m=m, y_shift=y_shift, w_shift=w_shift, split=split)
+        mz.mz_q4_gemm_ex(X.data_ptr(), m, N, K, wp, epi, 0 if epi == 5 else yp, stream(), pos=pos.data_ptr(),
+                         rope_cs=cs.data_ptr(), kv_off=off.data_ptr(), slab=yp if epi == 5 else 0, head_dim=hd,
+                         n_valid=N, chunk_tokens=C, **kw)
+        torch.cuda.synchronize()
+        n = y0.numel() * y0.element_size()
+        assert bool((buf[:256 + y_shift] == 0x55).all()) and bool((buf[256 + y_shift + n:] == 0x55).all())
+        return buf[256 + y_shift:256 + y_shift + n].clone()
+
+    esz = y0.element_size()
+    for split in (False, True):
+        ref = run(0, 0, split)
+        for shift in (esz, 8 + esz):
+            assert torch.equal(run(shift, 0, split), ref), (split, shift)
+        for shift in (2, 8):
+            got = run(0, shift, split)
+            if not split:
+                assert torch.equal(got, ref), shift
+                continue
+            a, b = got.view(y0.dtype).double(), ref.view(y0.dtype).double()
+            # the order of K fp32 sums, and for halves one rounding that may fall the other way
+            tol = K * 2.0 ** -24 if esz == 4 else 2.0 ** -10
+            assert float((a - b).abs().max()) <= tol * float(b.abs().max()), shift
+
+
 def _single_row_shapes(key):
     m = W.WORKLOADS[key].model
     ffp = (m.d_ffn + 127) // 128 * 128      # the SwiGLU output width, as the down projection reads it
