@@ -1011,7 +1011,7 @@ int gemm_splits(int k, int n_split) {
 // 128 x 128), and two workgroups per CU hide each other's start and end (1.5B
 // gate/up, 4979 rows: 255 us as 128 x 256, 284 as 256 x 256).
 struct GemmPlan {
-  int row_tile = 256, col_tile = 256, n_split = 1;
+  int rows = 0, row_tile = 256, col_tile = 256, n_split = 1;
   double us = 1e30;
 };
 
@@ -1058,7 +1058,7 @@ GemmPlan gemm_plan(int m, int n, int k, int64_t ws_cap, int max_split, bool rows
       const int ns = gemm_splits(k, want);
       if (ns > 1 && gemm_splitk_ws_bytes(m, n, ns) > ws_cap) break;
       const double us = plan_us(m, n, k, t, ns);
-      if (us < best.us) best = GemmPlan{t.row_tile, t.col_tile, ns, us};
+      if (us < best.us) best = GemmPlan{m, t.row_tile, t.col_tile, ns, us};
     }
   }
   return best;
@@ -1109,12 +1109,13 @@ void launch_reduce(const float* part, int ns, int m, int n, int epilogue, const 
   }
 }
 
-// Output rows [r0, r0 + m) of the product by a plan: the row-indexed
+// Output rows [r0, r0 + plan.rows) of the product by a plan: the row-indexed
 // pointers (row list or activations, output, RoPE positions and slot offsets)
 // are shifted.
 template <int EPI>
-void launch_planned(const GemmPlan& plan, const _Float16* X, const int32_t* a_rows, int r0, int m, int n, int k,
+void launch_planned(const GemmPlan& plan, const _Float16* X, const int32_t* a_rows, int r0, int n, int k,
                     const uint8_t* W, void* y, hipStream_t s, const GemmRope& ea, int* wq, void* ws) {
+  const int m = plan.rows;
   const _Float16* x = a_rows ? X : X + (size_t)r0 * k;
   const int32_t* ar = a_rows ? a_rows + r0 : nullptr;
   GemmRope e = ea;
@@ -1137,32 +1138,43 @@ void launch_planned(const GemmPlan& plan, const _Float16* X, const int32_t* a_ro
   }
 }
 
+// The launches of a product: one by the best plan of all its rows, or the
+// whole 256-row tiles and then the other rows by a plan of their own, since a
+// ragged last row of 256-row tiles can make a final round of workgroups that
+// occupies few CUs (16 column tiles x 129 row tiles = 8 rounds + 16
+// workgroups on 256 CUs).  Returns how many of p are used.
+int gemm_parts(int m, int n, int k, int64_t ws_bytes, int max_split, bool rows_ok, GemmPlan (&p)[2]) {
+  p[0] = gemm_plan(m, n, k, ws_bytes, max_split, rows_ok);
+  const int full = m / BM * BM, rem = m - full;
+  if (rem == 0 || full == 0) return 1;
+  const GemmPlan tail = gemm_plan(rem, n, k, ws_bytes, max_split, rows_ok);
+  const double us = plan_us(full, n, k, kTiles[0], 1);
+  if (!(us + tail.us < p[0].us)) return 1;
+  p[0] = GemmPlan{full, 256, 256, 1, us};
+  p[1] = tail;
+  return 2;
+}
+
 template <int EPI>
 void launch_epi(const _Float16* X, const int32_t* a_rows, int m, int n, int k, const uint8_t* W, void* y,
                 hipStream_t s, const GemmRope& ea = GemmRope{}, int* wq = nullptr, void* ws = nullptr,
                 int64_t ws_bytes = 0, int max_split = 32) {
-  const bool ok = gemm_rows_ok(W);
-  const int ns_cap = ws ? max_split : 1;
-  const GemmPlan whole = gemm_plan(m, n, k, ws_bytes, ns_cap, ok);
-  // A ragged last row of 256-row tiles can make a final round of workgroups
-  // that occupies few CUs (16 column tiles x 129 row tiles = 8 rounds + 16
-  // workgroups on 256 CUs).  Then the whole 256-row tiles run in one launch
-  // and the remaining rows by a plan of their own in a second one.
-  const int full = m / BM * BM, rem = m - full;
-  if (rem > 0 && full > 0) {
-    const GemmPlan tail = gemm_plan(rem, n, k, ws_bytes, ns_cap, ok);
-    if (plan_us(full, n, k, kTiles[0], 1) + tail.us < whole.us) {
-      launch_planned<EPI>(GemmPlan{}, X, a_rows, 0, full, n, k, W, y, s, ea, wq, ws);
-      launch_planned<EPI>(tail, X, a_rows, full, rem, n, k, W, y, s, ea, nullptr, ws);
-      return;
-    }
-  }
-  launch_planned<EPI>(whole, X, a_rows, 0, m, n, k, W, y, s, ea, wq, ws);
+  GemmPlan p[2];
+  const int np = gemm_parts(m, n, k, ws_bytes, ws ? max_split : 1, gemm_rows_ok(W), p);
+  launch_planned<EPI>(p[0], X, a_rows, 0, n, k, W, y, s, ea, wq, ws);
+  if (np > 1) launch_planned<EPI>(p[1], X, a_rows, p[0].rows, n, k, W, y, s, ea, nullptr, ws);
 }
 
 }  // namespace
 
 int64_t gemm_splitk_ws_bytes(int m, int n, int n_split) { return (int64_t)n_split * m * n * 4; }
+
+int gemm_pieces(int m, int n, int k, int64_t ws_bytes, GemmPiece (&out)[2]) {
+  GemmPlan p[2];
+  const int np = gemm_parts(m, n, k, ws_bytes, ws_bytes > 0 ? 32 : 1, true, p);
+  for (int i = 0; i < np; ++i) out[i] = GemmPiece{p[i].rows, p[i].row_tile, p[i].col_tile, p[i].n_split};
+  return np;
+}
 
 int gemm_auto_splits(int m, int n, int k, int64_t ws_cap) {
   const int bm = (n / BN) * ((m + 255) / 256) < 128 ? 64 : 256;

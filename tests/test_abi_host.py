@@ -186,8 +186,38 @@ def test_attention_auto_splits_decode_rows():
     assert mz.mz_attention_auto_splits(40000, 40000, 24, 8, 128, 64 << 20) == 1   # the chip is full already
 
 
+def test_gemm_plan():
+    """The launches of a product: rows, tile and K splits.  Each tile form
+    where the GPU tests rely on it; rows add up, splits fit the workspace and
+    need one, a tail follows whole 256-row tiles, and invalid sizes have no
+    plan."""
+    ws = 64 << 20
+    for m, tile in ((2, (32, 128)), (33, (32, 128)), (65, (64, 128)), (129, (128, 128))):
+        assert mz.mz_q4_gemm_plan(m, 16384, 192) == [(m, *tile, 1)]
+    assert mz.mz_q4_gemm_plan(4096, 16384, 192) == [(4096, 128, 256, 1)]
+    assert mz.mz_q4_gemm_plan(4096, 16384, 5440) == [(4096, 256, 256, 1)]
+    assert mz.mz_q4_gemm_plan(16400, 16384, 6016) == [(16384, 256, 256, 1), (16, 32, 128, 1)]
+    assert mz.mz_q4_gemm_plan(1000, 4096, 14336, ws) == [(1000, 128, 256, 4)]
+    assert mz.mz_q4_gemm_plan(2000, 4096, 14336, ws) == [(2000, 256, 256, 2)]
+    assert mz.mz_q4_gemm_plan(2000, 4096, 14336)[0][3] == 1
+    rng = np.random.default_rng(4)
+    for _ in range(2000):
+        m, n = int(2 ** rng.uniform(0, 15)), 256 * int(2 ** rng.uniform(0, 7))
+        k, wsb = 64 * int(2 ** rng.uniform(0, 8)), int(rng.choice([0, 1 << 20, ws]))
+        p = mz.mz_q4_gemm_plan(m, n, k, wsb)
+        assert sum(r[0] for r in p) == m and 1 <= len(p) <= 2, (m, n, k, wsb, p)
+        if len(p) == 2:
+            assert p[0][0] % 256 == 0 and p[0][1:] == (256, 256, 1), (m, n, k, wsb, p)
+        for rows, rt, ct, ns in p:
+            assert (rt, ct) in ((32, 128), (64, 128), (128, 128), (128, 256), (256, 256))
+            assert 1 <= ns <= min(32, k // 64) and (ns == 1 or ns * rows * n * 4 <= wsb), (m, n, k, wsb, p)
+    for bad in ((0, 256, 64, 0), (1, 128, 64, 0), (1, 300, 64, 0), (1, 256, 32, 0), (1, 256, 96, 0), (1, 256, 64, -1)):
+        assert mz.mz_q4_gemm_plan(*bad) == []
+
+
 def test_gemm_long_k_splits():
-    """256-row tiles split over K only where they alone are too few for the
+    """The long-K split count (no launch takes it; see mz_q4_gemm_plan for
+    those that run): 256-row tiles split over K only where they alone are too few for the
     chip, the 64-row tiles fill it, every split keeps 16 K steps and the
     partials fit the workspace: the 1B down projection (2048 rows, 2048
     outputs, K 8192) with the restore's 64 MiB takes 4 splits of 32 steps;

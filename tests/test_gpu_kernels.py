@@ -69,11 +69,11 @@ def _gemm_case(M, N, K, epi, seed, sample_rows=None, n_split=None):
             torch.cuda.synchronize()
             assert int(queues.abs().sum()) == 0, "work queues not left at zero"
             assert torch.equal(y.view(torch.uint8), plain.view(torch.uint8)), "queued != mz_q4_gemm"
-    elif n_split == "long-k":
+    elif n_split in ("long-k", "workspace"):
         wsb = 64 << 20
-        ns = mz.mz_q4_gemm_long_k_splits(M, n_pad, K, wsb)
-        report("  long-K splits", n_split=ns)
-        assert ns > 1, "shape outside the long-K split rule"
+        report("  plan", plan=mz.mz_q4_gemm_plan(M, n_pad, K, wsb))
+        if n_split == "long-k":
+            assert mz.mz_q4_gemm_long_k_splits(M, n_pad, K, wsb) > 1, "shape outside the long-K split rule"
         ws = torch.full((wsb // 4,), float("nan"), device="cuda")      # stale partials must not leak in
         mz.mz_q4_gemm_ex(x.data_ptr(), M, n_pad, K, w.data_ptr(), epi, y.data_ptr(), stream(),
                          workspace=ws.data_ptr(), workspace_bytes=wsb)
@@ -133,11 +133,25 @@ def test_gemm_split(M, N, K, epi):
                                        (2048, 1024, 8192, 2)])
 def test_gemm_long_k_split(M, N, K, epi):
     """Products with too few 256-row tiles for the chip but a long K range,
-    as the restore launches them (with its workspace): 256-row tiles split
-    over K.  The 1B down projection (4 splits of 32 K steps), a ragged last
-    row tile, 16 steps per split, and the SwiGLU epilogue, against the exact
-    product on one row in every 64-row tile."""
+    as the restore launches them (with its workspace): they run as 128 x 128
+    tiles over all of K (test_gemm_planned_splits has those that split).  The
+    1B down projection, a ragged last row tile, half the K range, and the
+    SwiGLU epilogue, against the exact product on one row in every 64-row
+    tile."""
+    assert [p[1:] for p in mz.mz_q4_gemm_plan(M, 2 * N if epi == 2 else N, K, 64 << 20)] == [(128, 128, 1)]
     _gemm_case(M, N, K, epi, seed=M + N + K + 5, sample_rows=_tile_rows(M, 64, M + K), n_split="long-k")
+
+
+@pytest.mark.parametrize("M,plan", [(17, (32, 128, 8)), (40, (64, 128, 8)), (128, (128, 128, 8)), (1000, (128, 256, 4)),
+                                    (1900, (128, 256, 2)), (1921, (256, 256, 2)), (2048, (256, 256, 2))])
+def test_gemm_planned_splits(M, plan):
+    """The 8B down projection as the restore launches it (64 MiB of workspace,
+    NaN before the call) in every tile form that splits over K, against the
+    exact product on one row in every 64-row tile; the plan says which form
+    runs."""
+    N, K = 4096, 14336
+    assert mz.mz_q4_gemm_plan(M, N, K, 64 << 20) == [(M, *plan)]
+    _gemm_case(M, N, K, 1, seed=M, sample_rows=_tile_rows(M, 64, M), n_split="workspace")
 
 
 @pytest.mark.parametrize("M", [1, 129])
@@ -184,10 +198,11 @@ def _tile_rows(M, tile, seed):
 
 @pytest.mark.parametrize("key", ["tiny", "1b", "3b", "1p5b", "8b"])
 def test_gemm_full_layer_shapes(key):
-    """Every projection of the workload at its full row count (the launch the
-    benchmark times), checked on one row in every 64-row tile (so in every
-    256- and 64-row tile of either launch form) including the ragged tail and
-    both sides of the row where whole 256-row tiles end."""
+    """Every projection of the workload at its full row count, checked on one
+    row in every 64-row tile (so in every tile but the 32-row ones) including
+    the ragged tail and both sides of the row where whole 256-row tiles end;
+    work queues passed as the restore does (a launch takes them where
+    test_gemm_queues_taken says) and bit-equal to mz_q4_gemm."""
     for i, (M, N, K, epi) in enumerate(_layer_gemms(key)):
         _gemm_case(M, N, K, epi, seed=100 + i, sample_rows=_tile_rows(M, 64, i), n_split="queued")
 
@@ -358,6 +373,9 @@ def test_gemm_tile_shapes_same_bits(epi, hd, K):
         torch.cuda.synchronize()
         return slab.view(-1, 2, slot // 4) if epi == 5 else y
 
+    assert mz.mz_q4_gemm_plan(M, N, K) == [(M, 128 if K == 192 else 256, 256, 1)]
+    small = {mz.mz_q4_gemm_plan(m, N, K)[0][1:3] for m in (1, 65, 300)}
+    assert small == {(32, 128), (64, 128), (128, 128)}
     full = run(M)
     assert bool((full != 0).any())
     for m in (1, 2, 31, 32, 33, 64, 65, 127, 128, 129, 300):
@@ -599,11 +617,12 @@ def test_gemv_validation():
     (20000, 14336, 128, 0), (16640, 16384, 64, 1), (20000, 7168, 128, 2), (33000, 8192, 64, 1),
     (1000, 2048, 512, 0), (9000, 4096, 512, 1), (300, 512, 128, 1)])
 def test_gemm_queued(M, N, K, epi):
-    """mz_q4_gemm_queued for every plain epilogue: launches of at least 16
-    rounds (4096 and more 256-row tiles) take the work queues, with and
-    without a ragged remainder of 64-row tiles; shorter ones run one
-    workgroup per tile.  Against the exact product on sampled rows and
-    bit-equal to mz_q4_gemm."""
+    """mz_q4_gemm_queued for every plain epilogue on products that run in
+    other tiles than 256 x 256, short K ranges of many rounds and small ones:
+    the queues stay untouched, one workgroup per tile (test_gemm_queues_taken
+    has the products that take them).  Against the exact product on sampled
+    rows and bit-equal to mz_q4_gemm."""
+    assert all(p[1:3] != (256, 256) for p in mz.mz_q4_gemm_plan(M, 2 * N if epi == 2 else N, K))
     rows = None
     if M > 4000:
         rng = np.random.default_rng(M)
@@ -611,6 +630,45 @@ def test_gemm_queued(M, N, K, epi):
                                          [0, M // 256 * 256 - 1, M // 256 * 256, M - 1]]))
         rows = rows[rows < M]   # M // 256 * 256 is M itself when M is a multiple of 256
     _gemm_case(M, N, K, epi, seed=M + 7, sample_rows=rows, n_split="queued")
+
+
+@pytest.mark.parametrize("M,epi", [(16400, 0), (16384, 1), (16400, 2)])
+def test_gemm_queues_taken(M, epi):
+    """Products whose plan is 256 x 256 tiles, 16 rounds of them and more (4096
+    tiles), take the work queues in the store, residual-add and SwiGLU
+    epilogue, with and without a ragged remainder in a second launch: the
+    bits of mz_q4_gemm, which runs them one workgroup per tile, and of the
+    rows at tile edges by themselves (32-row tiles); the queues come back
+    zero, twice."""
+    torch = torch_cuda()
+    N, K = 16384, 6016
+    plan = mz.mz_q4_gemm_plan(M, N, K)
+    assert plan[0] == (16384, 256, 256, 1) and 16384 // 256 * (N // 256) >= 4096, plan
+    gen = torch.Generator(device="cuda").manual_seed(M + epi)
+    X = torch.randn(M, K, device="cuda", generator=gen).half()
+    W_ = torch.randint(0, 256, (N // 256, K // 64, 9216), device="cuda", dtype=torch.uint8, generator=gen)
+    sc = (torch.rand(N // 256, K // 64, 512, device="cuda", generator=gen) * 0.01 + 0.01).half()
+    W_[..., 8192:] = sc.view(torch.uint8).view(N // 256, K // 64, 1024)
+    if epi == 1:
+        y0 = torch.randn(M, N, device="cuda", generator=gen)
+    else:
+        y0 = torch.zeros(M, N // 2 if epi == 2 else N, device="cuda", dtype=torch.float16 if epi == 2 else torch.float32)
+    plain = y0.clone()
+    report("queues taken", M=M, epi=epi, plan=plan)
+    mz.mz_q4_gemm(X.data_ptr(), M, N, K, W_.data_ptr(), epi, plain.data_ptr(), stream())
+    queues = torch.zeros(16, device="cuda", dtype=torch.int32)
+    y = torch.empty_like(y0)
+    for _ in range(2):
+        y.copy_(y0)
+        mz.mz_q4_gemm_queued(X.data_ptr(), M, N, K, W_.data_ptr(), epi, y.data_ptr(), queues.data_ptr(), stream())
+        torch.cuda.synchronize()
+        assert int(queues.abs().sum()) == 0, "work queues not left at zero"
+        assert torch.equal(y, plain), "queued != mz_q4_gemm"
+    rows = torch.tensor([0, 255, 256, 5000, 8191, 8192, 16383, M - 1], device="cuda")
+    few = y0[rows].contiguous()
+    mz.mz_q4_gemm(X[rows].contiguous().data_ptr(), len(rows), N, K, W_.data_ptr(), epi, few.data_ptr(), stream())
+    torch.cuda.synchronize()
+    assert bool((few != 0).any()) and torch.equal(few, y[rows])
 
 
 def _attn_case(nq, nkv, hd, C, S, qpos, seed, sample=None, n_split=None, n_table=None):
