@@ -456,11 +456,15 @@ mz_status mz_q4_gemv(const void *x_f16, int32_t k, const void *w_packed, int32_t
 /* Split-K form of mz_q4_gemm for few rows (the short requests of the
  * paper's evaluation, Sec. 6, and every decode step): a grid of output
  * tiles alone leaves most of the GPU idle there.  The k / 64 steps are cut
- * into at most n_split equal ranges (fewer, or one, where that is faster;
- * always the same for the same arguments); each range runs as its own
- * workgroups and leaves its fp32 sums in workspace; a second kernel
- * adds the ranges in order and applies the epilogue, so results are
- * deterministic and equal mz_q4_gemm's up to the order of the fp32 sums.
+ * into n_split ranges of ceil((k / 64) / n_split) steps (those that are not
+ * empty); each range runs as its own workgroups and leaves its fp32 sums in
+ * workspace; a second kernel adds the ranges in order and applies the
+ * epilogue, so results are deterministic and equal mz_q4_gemm's up to the
+ * order of the fp32 sums.
+ * With more than one row, the count that mz_q4_gemm_auto_splits gives for 64
+ * MiB of workspace (or workspace_bytes, if that is more) leaves the number to
+ * the call: at most n_split ranges, fewer or one where that is faster, always
+ * the same for the same m, n_pad, k and n_split.
  * workspace: device, caller-owned, at least
  * mz_q4_gemm_split_workspace_bytes(m, n_pad, n_split) bytes, not shared by
  * calls in flight together.  Other arguments and errors as mz_q4_gemm; EINVAL
@@ -478,12 +482,12 @@ int64_t mz_q4_gemm_split_workspace_bytes(int32_t m, int32_t n_pad, int32_t n_spl
 
 /* mz_q4_gemm_split for callers that cannot allocate device memory: code under
  * HIP graph capture, tight serving loops, hosts that forbid allocation.  The
- * same kernels and the same result bits as mz_q4_gemm_split with n_split, but
- * the fp32 partials go to a fixed device array of MZ_NOALLOC_SCRATCH_BYTES
- * that the library holds on each GPU it has run this call on, until the
- * process ends; the call allocates nothing.  The array's address on a device
- * is looked up on the first call there, with that device current.  stream
- * (NULL = the default stream) must belong to the current device.  Every call
+ * same kernels and the same result bits as mz_q4_gemm_split with n_split (and
+ * at most 64 MiB of workspace), but the fp32 partials go to a fixed device
+ * array of MZ_NOALLOC_SCRATCH_BYTES that the library holds on each GPU it has
+ * run this call on, until the process ends; the call allocates nothing.  The
+ * array's address on a device is looked up on the first call there, with that
+ * device current.  stream (NULL = the default stream) must belong to the current device.  Every call
  * on one GPU shares that GPU's array: calls that overlap on one GPU race
  * (serialize them, e.g. on one stream).  Errors: EINVAL as mz_q4_gemm_split,
  * and when n_split * m * n_pad * 4 bytes exceed MZ_NOALLOC_SCRATCH_BYTES or
@@ -496,8 +500,8 @@ mz_status mz_q4_gemm_split_noalloc(const void *x_f16, int32_t m, int32_t n_pad, 
 /* A split count for mz_q4_gemm_split with workspace_bytes of workspace: enough
  * for two workgroups of 64-row tiles per compute unit, at least 4 K steps per
  * split, at most 32 splits; 1 when the tile grid already fills the GPU, or
- * when m >= 1024 and the tiles cover half of its compute units.  Of these the
- * call takes the number that is fastest. */
+ * when m >= 1024 and the tiles cover half of its compute units.  A
+ * mz_q4_gemm_split with this count takes as many of them as are fastest. */
 int32_t mz_q4_gemm_auto_splits(int32_t m, int32_t n_pad, int32_t k, int64_t workspace_bytes);
 
 /* The launches that mz_q4_gemm (workspace_bytes 0) or mz_q4_gemm_ex with

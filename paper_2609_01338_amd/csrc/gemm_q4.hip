@@ -1041,6 +1041,18 @@ double plan_us(int m, int n, int k, const TileTimes& t, int ns) {
   return kLaunchUs + second + (gemm_k_steps(k, ns) + t.extra - 1) * steps + out + (ns > 1 ? kReduceUs + out : 0.);
 }
 
+// The plan of a product of m rows in exactly n_split ranges of K.
+GemmPlan gemm_plan_asked(int m, int n, int k, int n_split, bool rows_ok) {
+  GemmPlan best;
+  for (const TileTimes& t : kTiles) {
+    if (t.row_tile < 256 && !rows_ok) break;
+    if (t.row_tile > 32 && t.row_tile < 256 && t.row_tile >= 2 * m) continue;
+    const double us = plan_us(m, n, k, t, gemm_splits(k, n_split));
+    if (us < best.us) best = GemmPlan{m, t.row_tile, t.col_tile, n_split, us};
+  }
+  return best;
+}
+
 // The plan of a product of m rows with at most max_split splits whose
 // partials fit ws_cap bytes.  rows_ok: the tiles of gemm_rows.hip may run.
 GemmPlan gemm_plan(int m, int n, int k, int64_t ws_cap, int max_split, bool rows_ok) {
@@ -1176,6 +1188,10 @@ int gemm_pieces(int m, int n, int k, int64_t ws_bytes, GemmPiece (&out)[2]) {
   return np;
 }
 
+bool gemm_split_at_most(int m, int n, int k, int n_split, int64_t ws_bytes) {
+  return n_split == gemm_auto_splits(m, n, k, std::max<int64_t>(ws_bytes, (int64_t)64 << 20));
+}
+
 int gemm_auto_splits(int m, int n, int k, int64_t ws_cap) {
   const int bm = (n / BN) * ((m + 255) / 256) < 128 ? 64 : 256;
   const int tiles = (n / BN) * ((m + bm - 1) / bm);
@@ -1263,9 +1279,10 @@ namespace {
 
 template <int EPI>
 void launch_splitk(const void* x, int m, int n, int k, const void* w, const GemmRope& ea, void* y, int n_split,
-                   void* ws, hipStream_t s, const int32_t* a_rows, const float* h_norm, float eps) {
-  if (m == 1) {   // the split GEMV
-    const int ns = launch_partials(x, m, n, k, w, n_split, ws, s, a_rows, h_norm, eps, GemmPlan{});
+                   void* ws, hipStream_t s, const int32_t* a_rows, const float* h_norm, float eps, bool at_most) {
+  if (m == 1 || (n_split > 1 && !at_most)) {   // a single row: the split GEMV
+    const GemmPlan plan = m == 1 ? GemmPlan{} : gemm_plan_asked(m, n, k, n_split, gemm_rows_ok(w));
+    const int ns = launch_partials(x, m, n, k, w, n_split, ws, s, a_rows, h_norm, eps, plan);
     launch_reduce(reinterpret_cast<const float*>(ws), ns, m, n, EPI, ea, y, s);
     return;
   }
@@ -1279,18 +1296,19 @@ void launch_gemm_q4_splitk_rope(const void* x, int m, int n, int k, const void* 
                                 void* y, int n_split, void* ws, hipStream_t s, const int32_t* a_rows,
                                 const float* h_norm, float eps) {
   if (epilogue == kEpiRopeQ)
-    launch_splitk<kEpiRopeQ>(x, m, n, k, w, ea, y, n_split, ws, s, a_rows, h_norm, eps);
+    launch_splitk<kEpiRopeQ>(x, m, n, k, w, ea, y, n_split, ws, s, a_rows, h_norm, eps, false);
   else
-    launch_splitk<kEpiRopeKV>(x, m, n, k, w, ea, y, n_split, ws, s, a_rows, h_norm, eps);
+    launch_splitk<kEpiRopeKV>(x, m, n, k, w, ea, y, n_split, ws, s, a_rows, h_norm, eps, false);
 }
 
 void launch_gemm_q4_splitk(const void* x, int m, int n, int k, const void* w, int epilogue, void* y, int n_split,
-                           void* ws, hipStream_t s, const int32_t* a_rows, const float* h_norm, float eps) {
+                           void* ws, hipStream_t s, const int32_t* a_rows, const float* h_norm, float eps,
+                           bool at_most) {
   const GemmRope ea;
   switch (epilogue) {
-    case kEpiStore: launch_splitk<kEpiStore>(x, m, n, k, w, ea, y, n_split, ws, s, a_rows, h_norm, eps); break;
-    case kEpiAdd: launch_splitk<kEpiAdd>(x, m, n, k, w, ea, y, n_split, ws, s, a_rows, h_norm, eps); break;
-    default: launch_splitk<kEpiSwiGLU>(x, m, n, k, w, ea, y, n_split, ws, s, a_rows, h_norm, eps); break;
+    case kEpiStore: launch_splitk<kEpiStore>(x, m, n, k, w, ea, y, n_split, ws, s, a_rows, h_norm, eps, at_most); break;
+    case kEpiAdd: launch_splitk<kEpiAdd>(x, m, n, k, w, ea, y, n_split, ws, s, a_rows, h_norm, eps, at_most); break;
+    default: launch_splitk<kEpiSwiGLU>(x, m, n, k, w, ea, y, n_split, ws, s, a_rows, h_norm, eps, at_most); break;
   }
 }
 

@@ -68,16 +68,20 @@ struct GemmPiece {
 };
 int gemm_pieces(int m, int n, int k, int64_t ws_bytes, GemmPiece (&out)[2]);
 
-// Split-K form for few rows: at most n_split ranges of whole 64-wide K steps
-// (fewer, or none, where the plan is faster; a single row exactly
-// gemm_splits(k, n_split)) write fp32 partials into ws (gemm_splitk_ws_bytes(m,
-// n, n_split) bytes), then one kernel adds them in split order and applies
-// the epilogue.  h_norm (m == 1 only): x is not read; the row is
-// RMSNorm(h_norm row, eps) formed inside the product, the same f16 values
-// launch_rmsnorm writes.
+// Split-K form for few rows: gemm_splits(k, n_split) ranges of whole 64-wide
+// K steps, as many of n_split equal ones as are not empty, write fp32 partials
+// into ws (gemm_splitk_ws_bytes(m, n, n_split) bytes), then one kernel adds
+// them in split order and applies the epilogue.  at_most (more than one row):
+// fewer splits, or none, where launch_gemm_q4's plan is faster so.  h_norm
+// (m == 1 only): x is not read; the row is RMSNorm(h_norm row, eps) formed
+// inside the product, the same f16 values launch_rmsnorm writes.
 void launch_gemm_q4_splitk(const void* x, int m, int n, int k, const void* w, int epilogue, void* y, int n_split,
                            void* ws, hipStream_t s, const int32_t* a_rows = nullptr,
-                           const float* h_norm = nullptr, float eps = 0.f);
+                           const float* h_norm = nullptr, float eps = 0.f, bool at_most = false);
+// Whether a caller's split count leaves the number to the plan: it is the
+// one that gemm_auto_splits gives, with 64 MiB of workspace or the caller's if
+// that is larger.
+bool gemm_split_at_most(int m, int n, int k, int n_split, int64_t ws_bytes);
 int64_t gemm_splitk_ws_bytes(int m, int n, int n_split);
 // Split-K form with a rotary-embedding epilogue (kEpiRopeQ / kEpiRopeKV): the
 // splits are added in order, then rotated and written as the unsplit

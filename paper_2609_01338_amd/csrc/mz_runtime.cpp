@@ -1978,8 +1978,9 @@ mz_status mz_q4_gemm_split(const void* x_f16, int32_t m, int32_t n_pad, int32_t 
     if (n_split < 1 || n_split > 1024) fail(MZ_EINVAL, "n_split must be 1..1024");
     if (workspace_bytes < mzk::gemm_splitk_ws_bytes(m, n_pad, n_split))
       fail(MZ_EINVAL, "workspace too small for %d splits", n_split);
-    mzk::launch_gemm_q4_splitk(x_f16, m, n_pad, k, w_packed, epilogue, y, n_split, workspace,
-                               (hipStream_t)stream);
+    mzk::launch_gemm_q4_splitk(x_f16, m, n_pad, k, w_packed, epilogue, y, n_split, workspace, (hipStream_t)stream,
+                               nullptr, nullptr, 0.f,
+                               mzk::gemm_split_at_most(m, n_pad, k, n_split, workspace_bytes));
     HIPCHK(hipGetLastError());
   });
 }

@@ -80,7 +80,8 @@ extern "C" mz_status mz_q4_gemm_split_noalloc(const void* x_f16, int32_t m, int3
   void* ws = nullptr;
   const mz_status st = scratch_address(&ws);
   if (st != MZ_OK) return st;
-  mzk::launch_gemm_q4_splitk(x_f16, m, n_pad, k, w_packed, epilogue, y, n_split, ws, s);
+  mzk::launch_gemm_q4_splitk(x_f16, m, n_pad, k, w_packed, epilogue, y, n_split, ws, s, nullptr, nullptr, 0.f,
+                             mzk::gemm_split_at_most(m, n_pad, k, n_split, 0));
   if (hipGetLastError() != hipSuccess) {
     mzrt::set_error("kernel launch failed");
     return MZ_EHIP;

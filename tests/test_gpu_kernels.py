@@ -154,6 +154,39 @@ def test_gemm_planned_splits(M, plan):
     _gemm_case(M, N, K, 1, seed=M, sample_rows=_tile_rows(M, 64, M), n_split="workspace")
 
 
+@pytest.mark.parametrize("m,N,K", [(2, 512, 704), (17, 1024, 2048), (200, 768, 1088), (1500, 512, 1024)])
+def test_gemm_split_count_kept(m, N, K):
+    """A split count other than mz_q4_gemm_auto_splits' own is taken as it is:
+    the ranges of ceil(steps / n_split) steps, each the bits of mz_q4_gemm on
+    its part of K, added in order in fp32.  Down to one step per range,
+    trailing empty ranges and one range among them."""
+    torch = torch_cuda()
+    nk = K // 64
+    gen = torch.Generator(device="cuda").manual_seed(m)
+    X = torch.randn(m, K, device="cuda", generator=gen).half()
+    W_ = torch.randint(0, 256, (N // 256, nk, 9216), device="cuda", dtype=torch.uint8, generator=gen)
+    sc = (torch.rand(N // 256, nk, 512, device="cuda", generator=gen) * 0.01 + 0.01).half()
+    W_[..., 8192:] = sc.view(torch.uint8).view(N // 256, nk, 1024)
+    auto = mz.mz_q4_gemm_auto_splits(m, N, K, 64 << 20)
+    for n_split in sorted({1, 2, 3, 5, nk - 1, nk, nk + 5} - {auto}):
+        report("split count", m=m, N=N, K=K, n_split=n_split)
+        y = torch.zeros(m, N, device="cuda")
+        wsb = mz.mz_q4_gemm_split_workspace_bytes(m, N, n_split)
+        ws = torch.full((wsb // 4,), float("nan"), device="cuda")
+        mz.mz_q4_gemm_split(X.data_ptr(), m, N, K, W_.data_ptr(), 0, y.data_ptr(), n_split, ws.data_ptr(), wsb,
+                            stream())
+        ref = None
+        steps = (nk + n_split - 1) // n_split
+        for k0 in range(0, nk, steps):
+            k1 = min(k0 + steps, nk)
+            xs, wp = X[:, k0 * 64:k1 * 64].contiguous(), W_[:, k0:k1].contiguous()
+            part = torch.zeros(m, N, device="cuda")
+            mz.mz_q4_gemm(xs.data_ptr(), m, N, (k1 - k0) * 64, wp.data_ptr(), 0, part.data_ptr(), stream())
+            torch.cuda.synchronize()
+            ref = part if ref is None else ref + part
+        assert bool((ref != 0).any()) and torch.equal(y, ref), n_split
+
+
 @pytest.mark.parametrize("M", [1, 129])
 def test_gemm_split_8b_layer(M):
     """The 8B projections at a decode step (1 row) and a 128-token prompt
