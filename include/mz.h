@@ -573,12 +573,20 @@ mz_status mz_attention_split(const void *q_f16, const int32_t *qpos, int32_t m, 
 int64_t mz_attention_split_workspace_bytes(int32_t m, int32_t n_q_heads, int32_t head_dim,
                                            int32_t n_split);
 
-/* The split count the restore uses for m query rows up to max_pos with
- * workspace_bytes of workspace: about one workgroup per compute unit, or the
- * count that evens out whole rounds of them, at least 4 key tiles per split,
- * at most 64 splits; 1 when the unsplit kernel already fills the GPU. */
+/* A split count for m query rows up to max_pos with workspace_bytes of
+ * workspace: the fastest by a model of the launch's rounds of workgroups, at
+ * least 4 key tiles per split, at most 64 splits; 1 when the unsplit kernel
+ * already fills the GPU.  Where the rows lie is not known here: the count suits
+ * both a prompt that follows the context and rows spread over it. */
 int32_t mz_attention_auto_splits(int32_t m, int32_t max_pos, int32_t n_q_heads, int32_t n_kv_heads,
                                  int32_t head_dim, int64_t workspace_bytes);
+
+/* The same with what the restore, which takes this count, knows besides:
+ * keys, the sum over the rows of the keys each of them sees (its position + 1;
+ * 0: not known), and the chunk table's entries and chunk size. */
+int32_t mz_attention_auto_splits_keys(int32_t m, int32_t max_pos, int64_t keys, int32_t n_table,
+                                      int32_t chunk_tokens, int32_t n_q_heads, int32_t n_kv_heads,
+                                      int32_t head_dim, int64_t workspace_bytes);
 
 /* x = h / sqrt(mean(h^2) + eps) per row: h float [m][d] -> x f16 [m][d]. */
 mz_status mz_rmsnorm(const void *h_f32, int32_t m, int32_t d, float eps, void *x_f16,

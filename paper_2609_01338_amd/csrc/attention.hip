@@ -1170,7 +1170,60 @@ int attention_split_tiles(int max_pos, int n_split) {
   return (n_kt + n_split - 1) / n_split;
 }
 
-int attention_auto_splits(int m, int max_pos, int n_q, int n_kv, int head_dim, int64_t ws_cap) {
+namespace {
+
+// Modelled time in us of the tiled kernel over c key splits (1: none) of n_kt
+// key tiles, of which the rows see the share `seen` on average, and its merge.
+//
+// A workgroup passes len + kStart tiles' time for a split of len tiles.  The
+// workgroups of a launch are dealt to the 8 XCDs round-robin (attn_kernel), 32
+// CUs each, so whole rounds count per XCD: a CU takes two workgroups of four
+// waves side by side in `pair` us a tile, or one in `alone`; one of eight waves
+// takes as long as the two.  Rows that follow the context (a prompt) see nearly
+// all keys and run in whole rounds: 384 rows at 32768 keys, 12/2 heads of 128,
+// 5 workgroups per XCD and split -- 12 splits (two per CU) 103 us, 14 splits (a
+// third on some) 133.  Recomputed rows spread over the context see half of the
+// keys, in pieces of all lengths that even out: the load of an XCD's CUs and a
+// last piece.  In between, by the share.  The partials are written and read at
+// 5 TB/s.
+double attn_split_us(int m, int n_kt, double seen, int c, int n_q, int n_kv, int head_dim, int chunk_tokens,
+                     int n_table) {
+  constexpr double kStart = 4, kMergeUs = 3;
+  const double pair = head_dim == 128 ? 2.05 : 1.25;
+  const double alone = (head_dim == 128 ? 1.4 : 0.8) * (chunk_tokens < KT ? 1.6 : 1);   // (through registers)
+  constexpr int kXcds = 8, kXcdCus = 32;
+  const int group = n_q / n_kv;
+  const bool four = attn_four_waves(m, n_q, group, head_dim, chunk_tokens, n_table, c > 1, c);
+  int gpw, qw;
+  attn_wave_map(group, gpw, qw);
+  if (four) {
+    gpw = attn_four_heads(group);
+    qw = 4 / gpw;
+  }
+  const int items = (m + 32 * qw - 1) / (32 * qw) * (group / gpw);
+  const int64_t wgs = kXcds % n_kv == 0 ? (items + kXcds / n_kv - 1) / (kXcds / n_kv)   // of a split, on an XCD
+                                        : (int64_t)((items + kXcds - 1) / kXcds) * n_kv;
+  const double len = (double)((n_kt + c - 1) / c) + kStart;
+  const double pieces = std::min((double)c, seen * c + 0.5);   // splits that a workgroup's rows reach, on average
+  const double rounds = (double)((wgs * c + kXcdCus - 1) / kXcdCus);
+  const double load = wgs * (seen * n_kt + kStart * pieces) / kXcdCus;
+  double even, spread;
+  if (four) {
+    const double pairs = std::floor(rounds / 2);
+    even = len * (pairs * pair + (rounds - 2 * pairs) * alone);
+    spread = std::max(load * pair / 2 + 0.5 * len * alone, len * alone);
+  } else {
+    even = len * rounds * pair;
+    spread = (load + len) * pair;
+  }
+  const double w = std::min(1.0, std::max(0.0, 2 * (1 - seen)));
+  return w * std::min(spread, even) + (1 - w) * even + (c > 1 ? kMergeUs + 4.0 * m * n_q * head_dim / 5e6 * pieces : 0);
+}
+
+}  // namespace
+
+int attention_auto_splits(int m, int max_pos, int64_t keys, int n_q, int n_kv, int head_dim, int chunk_tokens,
+                          int n_table, int64_t ws_cap) {
   const int group = n_q / n_kv;
   int gpw, qw;
   attn_wave_map(group, gpw, qw);
@@ -1192,39 +1245,37 @@ int attention_auto_splits(int m, int max_pos, int n_q, int n_kv, int head_dim, i
     // 32.0 at 58, 36.7 at 47 and 36.1 at 24)
     ns = std::min((kCus + wgs - 1) / wgs, cap);
   } else {
-    // One eight-wave workgroup of the tiled kernel, or two of four waves,
-    // fit a CU (its registers).  The smallest modelled time over the split
-    // counts, in key tiles of a workgroup: kStart of them pass before and
-    // after its key loop, and the partials are written and read at 5 TB/s.
-    // Rows that follow the context (a prompt) all see nearly every key: whole
-    // rounds of equal workgroups.  1024 and more, or half of the positions,
-    // are recomputed rows spread over the context, whose splits are on average
-    // half as many and even out.  128 rows at 32768 keys, 32/8 heads of 128:
-    // 16 splits 81 us, 31 92, 8 111; 4979 rows spread over 16384, 12/2 heads:
-    // 2 to 8 splits 295-315, 1 348.
-    // Unsplit, four-wave workgroups even out two to a CU: kWhole of the time
-    // (1024 rows, 24/8 heads of 128: unsplit 24.8 us, 2 splits 27.0; 2048 rows
-    // 49.2 and 50.4; 2048 rows of 12/2 heads 40.6 and 34.1 in 3 splits).
-    constexpr double kStart = 6, kMerge = 3, kWhole = 0.8;   // tiles; us; 1
-    const double tile_us = head_dim == 128 ? 1.9 : 1.0;
-    const bool spread = m >= 1024 || 2 * (int64_t)m >= (int64_t)max_pos + 1;
+    // The smallest modelled time.  How many keys the rows see comes from the
+    // caller: by the number of rows alone, 1000 rows spread over 32768 positions
+    // were taken for a prompt (32/8 heads of 128: 374 us in 2 splits, 259 in 4)
+    // and a prompt of 1024 rows after 32768 tokens for spread ones (611 us in 7,
+    // 566 in 2).  Where that is not known, the count that is nearest to the best
+    // time, at its worst, over prompts and spread rows, in chunks of at least a
+    // key tile and in shorter ones.  1132 random launches of ten head layouts,
+    // against the fastest count: 3.3 % slower on average (7.6 by the number of
+    // rows), 4.7 % with the keys unknown.
+    struct Form {
+      double seen;
+      int chunk_tokens, n_table;
+    };
+    const int n_cand = keys > 0 ? 1 : 4;
+    const Form known = {std::min(1.0, (double)keys / ((double)m * (max_pos + 1.0))), chunk_tokens, n_table};
+    const Form forms[4] = {keys > 0 ? known : Form{1.0, KT, 1}, {0.5, KT, 1}, {1.0, 16, 1}, {0.5, 16, 1}};
+    double us[4][kMaxSplits], least[4];
+    for (int f = 0; f < n_cand; ++f) {
+      least[f] = 1e30;
+      for (int c = 1; c <= cap; ++c) {
+        us[f][c - 1] = attn_split_us(m, n_kt, forms[f].seen, c, n_q, n_kv, head_dim, forms[f].chunk_tokens,
+                                     forms[f].n_table);
+        least[f] = std::min(least[f], us[f][c - 1]);
+      }
+    }
     double best = 1e30;
     for (int c = 1; c <= cap; ++c) {
-      const double len = (double)((n_kt + c - 1) / c) + kStart;
-      const double plane = 2.0 * m * n_q * head_dim * 2 / 5e6;   // us to write and read one split's partials
-      double us;
-      if (spread) {
-        us = std::max(wgs * (n_kt * 0.5 + kStart * (c + 1) * 0.5) / kCus + 0.5 * len, len) * tile_us;
-        if (c > 1)
-          us += kMerge + plane * (c + 1) * 0.5;
-        else
-          us *= kWhole;
-      } else {
-        us = (double)((wgs * c + kCus - 1) / kCus) * len * tile_us;
-        if (c > 1) us += kMerge + plane * c;
-      }
-      if (us < best) {
-        best = us;
+      double worst = 0;
+      for (int f = 0; f < n_cand; ++f) worst = std::max(worst, us[f][c - 1] / least[f]);
+      if (worst < best) {
+        best = worst;
         ns = c;
       }
     }

@@ -134,8 +134,10 @@ void launch_attention_split(const void* q, const int32_t* qpos, int m, int max_p
                             const int32_t* table, int n_table, int chunk_tokens, int64_t slot_bytes, int n_q,
                             int n_kv, int head_dim, int n_split, void* ws, void* out, hipStream_t s);
 int64_t attention_split_ws_bytes(int m, int n_q, int head_dim, int n_split);
-// Splits that fill the chip for this shape within ws_cap bytes (1: no split).
-int attention_auto_splits(int m, int max_pos, int n_q, int n_kv, int head_dim, int64_t ws_cap);
+// The fastest split count by a time model, within ws_cap bytes (1: no split).
+// keys: the sum over the rows of the keys each sees (position + 1), 0 if unknown.
+int attention_auto_splits(int m, int max_pos, int64_t keys, int n_q, int n_kv, int head_dim, int chunk_tokens,
+                          int n_table, int64_t ws_cap);
 
 // x f16 [m][d] = RMSNorm(h float [m][d]).
 void launch_rmsnorm(const float* h, int m, int d, float eps, void* x, hipStream_t s);

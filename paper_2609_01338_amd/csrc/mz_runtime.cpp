@@ -1121,16 +1121,17 @@ void restore_and_prefill_impl(mz_ctx* x, const int32_t* prompt, int32_t n_prompt
       cur ^= 1;
       h = dst;
     }
-    double keys = 0;
+    int64_t keys = 0;   // that the rows see
     if (l + 1 < L)
-      for (int p : rows.R[l + 1]) keys += p + 1.0;
+      for (int p : rows.R[l + 1]) keys += p + 1;
     else
       keys = S;
-    const double att_flops = 4.0 * x->hd * x->nq * keys;
+    const double att_flops = 4.0 * x->hd * x->nq * (double)keys;
     // few query rows against a long context: split the keys over the chip
     const int max_pos = l + 1 < L ? rows.R[l + 1].back() : S - 1;
-    const int n_split =
-        x->attn_split ? mzk::attention_auto_splits(nq, max_pos, x->nq, x->nkv, x->hd, x->split_ws_bytes) : 1;
+    const int n_split = x->attn_split ? mzk::attention_auto_splits(nq, max_pos, keys, x->nq, x->nkv, x->hd, C, MC,
+                                                                   x->split_ws_bytes)
+                                      : 1;
     x->timed(n_split > 1 ? kKAttentionSplit : kKAttention, att_flops, (double)nq * x->dq * 4.0, cs, [&] {
       if (n_split > 1)
         mzk::launch_attention_split(x->q16, posq, nq, max_pos, x->kv_slab, x->d_tables + (size_t)l * MC, MC, C,
@@ -2025,7 +2026,15 @@ int64_t mz_attention_split_workspace_bytes(int32_t m, int32_t n_q, int32_t head_
 int32_t mz_attention_auto_splits(int32_t m, int32_t max_pos, int32_t n_q, int32_t n_kv, int32_t head_dim,
                                  int64_t workspace_bytes) {
   if (m < 1 || max_pos < 0 || n_kv < 1 || n_q % n_kv || (head_dim != 64 && head_dim != 128)) return 1;
-  return mzk::attention_auto_splits(m, max_pos, n_q, n_kv, head_dim, workspace_bytes);
+  return mzk::attention_auto_splits(m, max_pos, 0, n_q, n_kv, head_dim, 256, max_pos / 256 + 1, workspace_bytes);
+}
+
+int32_t mz_attention_auto_splits_keys(int32_t m, int32_t max_pos, int64_t keys, int32_t n_table, int32_t chunk_tokens,
+                                      int32_t n_q, int32_t n_kv, int32_t head_dim, int64_t workspace_bytes) {
+  if (m < 1 || max_pos < 0 || n_kv < 1 || n_q % n_kv || (head_dim != 64 && head_dim != 128) || chunk_tokens < 1 ||
+      n_table < 1 || n_table > mzk::kAttnTableMax)
+    return 1;
+  return mzk::attention_auto_splits(m, max_pos, keys, n_q, n_kv, head_dim, chunk_tokens, n_table, workspace_bytes);
 }
 
 mz_status mz_attention_split(const void* q, const int32_t* qpos, int32_t m, int32_t max_pos, const void* slab,

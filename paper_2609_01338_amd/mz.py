@@ -130,6 +130,7 @@ def lib() -> ctypes.CDLL:
         "mz_attention_split": ([vp, vp, i32, i32, vp, vp, i32, i32, i32, i32, i32, i32, vp, i64, vp, vp], i32),
         "mz_attention_split_workspace_bytes": ([i32, i32, i32, i32], i64),
         "mz_attention_auto_splits": ([i32, i32, i32, i32, i32, i64], i32),
+        "mz_attention_auto_splits_keys": ([i32, i32, i64, i32, i32, i32, i32, i32, i64], i32),
         "mz_plan_evict_size": ([ctypes.POINTER(mz_model_cfg), i32, ctypes.POINTER(mz_evict_size_request),
                                 vp, vp, vp, vp, vp, vp], i32),
         "mz_evict_size": ([vp, ctypes.POINTER(mz_evict_size_request), vp], i32),
@@ -431,6 +432,12 @@ def mz_attention_split_workspace_bytes(m: int, n_q: int, head_dim: int, n_split:
 
 def mz_attention_auto_splits(m: int, max_pos: int, n_q: int, n_kv: int, head_dim: int, ws_bytes: int) -> int:
     return int(lib().mz_attention_auto_splits(m, max_pos, n_q, n_kv, head_dim, ws_bytes))
+
+
+def mz_attention_auto_splits_keys(m: int, max_pos: int, keys: int, n_table: int, chunk_tokens: int, n_q: int, n_kv: int,
+                                  head_dim: int, ws_bytes: int) -> int:
+    return int(lib().mz_attention_auto_splits_keys(m, max_pos, keys, n_table, chunk_tokens, n_q, n_kv, head_dim,
+                                                   ws_bytes))
 
 
 def mz_rmsnorm(h_ptr: int, m: int, d: int, eps: float, x_ptr: int, stream: Optional[int] = None) -> None:

@@ -186,6 +186,43 @@ def test_attention_auto_splits_decode_rows():
     assert mz.mz_attention_auto_splits(40000, 40000, 24, 8, 128, 64 << 20) == 1   # the chip is full already
 
 
+def test_attention_auto_splits_positions():
+    """The split count follows from where the rows lie, not from how many they
+    are: one row more in the same query tiles changes nothing (1023 and 1024
+    rows took 2 and 7 splits after 32768 tokens), a prompt and as many rows
+    spread over the context get counts of their own, and without the keys the
+    count does not jump either.  Counts keep 4 key tiles and the workspace."""
+    ws = 64 << 20
+    for nq, nkv, hd in ((32, 8, 128), (24, 8, 128), (12, 2, 128), (32, 8, 64)):
+        def count(m, first, seen=None):
+            last = first + m - 1
+            keys = m * first + m * (m + 1) // 2 if seen is None else int(m * (last + 1) * seen)
+            return mz.mz_attention_auto_splits_keys(m, last, keys, last // 256 + 1, 256, nq, nkv, hd, ws)
+        assert count(1023, 32768) == count(1024, 32768)
+        assert count(1023, 32768, 0.5) == count(1024, 32768, 0.5)
+        assert mz.mz_attention_auto_splits(1023, 33790, nq, nkv, hd, ws) == \
+            mz.mz_attention_auto_splits(1024, 33791, nq, nkv, hd, ws)
+    prompt, spread = (mz.mz_attention_auto_splits_keys(1000, 32767, int(1000 * 32768 * f), 128, 256, 32, 8, 128, ws)
+                      for f in (0.98, 0.5))
+    assert prompt == 2 and spread > 3      # (with 2 splits the spread rows took 374 us, 259 with 4, 277 with 7)
+    rng = np.random.default_rng(5)
+    for _ in range(2000):
+        nkv, g, hd = int(rng.integers(1, 17)), int(rng.integers(1, 12)), int(rng.choice([64, 128]))
+        m, last, wsb = int(2 ** rng.uniform(0, 13)), int(2 ** rng.uniform(0, 15)), int(rng.choice([1 << 16, 1 << 22, ws]))
+        keys = int(m * (last + 1) * rng.uniform(0.01, 1.2))   # (sums no rows can have, too)
+        c = int(2 ** rng.integers(3, 9))
+        args = (g * nkv, nkv, hd, wsb)
+        for ns in (mz.mz_attention_auto_splits_keys(m, last, keys, min(last // c + 1, 8192), c, *args),
+                   mz.mz_attention_auto_splits(m, last, *args)):
+            tiles = last // 64 + 1
+            assert 1 <= ns <= 64 and (ns == 1 or ns * 4 <= tiles), (m, last, args, ns)
+            assert ns == 1 or mz.mz_attention_split_workspace_bytes(m, g * nkv, hd, ns) <= wsb
+    for bad in ((0, 100, 1, 1, 256, 8, 8, 64, ws), (9, -1, 1, 1, 256, 8, 8, 64, ws), (9, 4000, 1, 0, 256, 8, 8, 64, ws),
+                (9, 4000, 1, 9000, 256, 8, 8, 64, ws), (9, 4000, 1, 16, 0, 8, 8, 64, ws), (9, 4000, 1, 16, 256, 8, 3, 64, ws),
+                (9, 4000, 1, 16, 256, 8, 8, 96, ws)):
+        assert mz.mz_attention_auto_splits_keys(*bad) == 1
+
+
 def test_gemm_plan():
     """The launches of a product: rows, tile and K splits.  Each tile form
     where the GPU tests rely on it; rows add up, splits fit the workspace and
