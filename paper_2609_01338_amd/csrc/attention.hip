@@ -510,9 +510,10 @@ __device__ __forceinline__ void attn_tile(const _Float16* __restrict__ Q, const 
   if (kt < kt_end) step(kt, s0, s1);
 
   const float l = l_i + __shfl_xor(l_i, 32);
-  const float inv = SPLIT ? (l > 0.f ? 1.0f / l : 0.f) : 1.0f / l;
+  // (a sum that is NaN is no empty range: it has to reach the output)
+  const float inv = SPLIT ? (l != 0.f ? 1.0f / l : 0.f) : 1.0f / l;
   if constexpr (SPLIT) {
-    if (qvalid && half == 0) MLpart[(size_t)(split * M + qi) * nq + h] = make_float2(l > 0.f ? m_i : -INFINITY, l);
+    if (qvalid && half == 0) MLpart[(size_t)(split * M + qi) * nq + h] = make_float2(l != 0.f ? m_i : -INFINITY, l);
   }
   if (qvalid) {
     _Float16* orow = SPLIT ? Opart + ((size_t)(split * M + qi) * nq + h) * HD : O + (size_t)qi * nq * HD + h * HD;
@@ -823,8 +824,9 @@ __global__ __launch_bounds__(64 * kFewWaves) void attn_few_kernel(
   }
   const int r_ = c / group, h_ = kvh * group + c % group;
   const size_t e0 = (size_t)split * M * nq + (size_t)r_ * nq + h_;
-  if (t < 16) MLpart[e0] = make_float2(den > 0.f ? mx : -INFINITY, den);
-  const float inv = den > 0.f ? 1.0f / den : 0.f;
+  // (NaN scores leave no maximum, and a sum that is NaN: a finite stand-in keeps the range in the merge)
+  if (t < 16) MLpart[e0] = make_float2(den != 0.f ? (mx == -INFINITY ? 0.f : mx) : -INFINITY, den);
+  const float inv = den != 0.f ? 1.0f / den : 0.f;
   constexpr int DPT = HD / (4 * kFewWaves);    // output dimensions per thread (64 * waves / 16 threads per column)
   const int dbase = (t >> 4) * DPT;
 #pragma unroll
@@ -877,7 +879,7 @@ __global__ __launch_bounds__(256) void attn_merge_wide_kernel(const _Float16* __
   float mx = -INFINITY;
 #pragma unroll
   for (int k = 0; k < 16; ++k) {
-    if (!(sg + 4 * k < nv && ml[k].y > 0.f)) ml[k].x = -INFINITY;
+    if (!(sg + 4 * k < nv && ml[k].y != 0.f)) ml[k].x = -INFINITY;
     mx = fmaxf(mx, ml[k].x);
   }
   if (dl == 0) s_m[sg] = mx;
@@ -936,7 +938,7 @@ __global__ __launch_bounds__(256) void attn_merge_rows_kernel(const _Float16* __
   float mx = -INFINITY;
 #pragma unroll
   for (int k = 0; k < R; ++k) {
-    if (!(gl + k * LPE < nv && ml[k].y > 0.f)) ml[k].x = -INFINITY;   // past the row's splits, or nothing seen
+    if (!(gl + k * LPE < nv && ml[k].y != 0.f)) ml[k].x = -INFINITY;   // past the row's splits, or nothing seen
     mx = fmaxf(mx, ml[k].x);
   }
 #pragma unroll

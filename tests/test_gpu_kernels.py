@@ -918,6 +918,41 @@ def test_attention_split_nonfinite_values(m):
     assert float((split - plain)[ok].abs().max()) <= 3 * 2.0 ** -10 * vmax
 
 
+@pytest.mark.parametrize("m", [2, 100, 400])
+def test_attention_split_nan_keys(m):
+    """A NaN key makes every output of its KV head NaN in the plain form, and
+    so in the split form (2 rows: the few-column kernel; 100 and 400: the tiled
+    one with either merge): a range whose sum is NaN is not one without keys.
+    Two NaN keys, one among other keys of its range and one range whose keys
+    are all NaN; the other KV head is untouched."""
+    torch = torch_cuda()
+    nq, nkv, hd, C, S, n_split = 8, 2, 64, 64, 1024, 8
+    n = S // C
+    gen = torch.Generator(device="cuda").manual_seed(m)
+    q = torch.randn(m, nq * hd, device="cuda", generator=gen).half()
+    table = torch.arange(n, device="cuda", dtype=torch.int32)
+    pos = torch.arange(S - m, S, device="cuda", dtype=torch.int32)
+    wsb = mz.mz_attention_split_workspace_bytes(m, nq, hd, n_split)
+    for whole in (False, True):
+        K = torch.randn(n, C, nkv * hd, device="cuda", generator=gen)
+        V = torch.randn(n, nkv * hd, C, device="cuda", generator=gen)
+        if whole:
+            K[2:4, :, :hd] = float("nan")                # keys 128..255: one range of eight
+        else:
+            K[1, 7, 3] = float("nan")
+        slab = torch.cat([K.reshape(n, -1), V.reshape(n, -1)], 1).half()
+        args = (slab.data_ptr(), table.data_ptr(), n, C, nq, nkv, hd)
+        plain, split = torch.zeros_like(q), torch.zeros_like(q)
+        mz.mz_attention(q.data_ptr(), pos.data_ptr(), m, *args, plain.data_ptr(), stream())
+        ws = torch.empty(wsb, device="cuda", dtype=torch.uint8)
+        mz.mz_attention_split(q.data_ptr(), pos.data_ptr(), m, S - 1, *args, n_split, ws.data_ptr(), wsb,
+                              split.data_ptr(), stream())
+        torch.cuda.synchronize()
+        half = nq // nkv * hd
+        for o in (plain, split):
+            assert bool(torch.isnan(o[:, :half]).all()) and bool(torch.isfinite(o[:, half:]).all()), whole
+
+
 @pytest.mark.parametrize("nq,nkv,hd,C,line", [(32, 8, 128, 64, 3072), (24, 8, 128, 256, 4096), (48, 8, 64, 64, 2048),
                                               (32, 8, 64, 16, 1024), (40, 8, 128, 128, 2457)])
 def test_attention_wave_count_line(nq, nkv, hd, C, line):
