@@ -1251,18 +1251,19 @@ int attention_auto_splits(int m, int max_pos, int64_t keys, int n_q, int n_kv, i
     // caller: by the number of rows alone, 1000 rows spread over 32768 positions
     // were taken for a prompt (32/8 heads of 128: 374 us in 2 splits, 259 in 4)
     // and a prompt of 1024 rows after 32768 tokens for spread ones (611 us in 7,
-    // 566 in 2).  Where that is not known, the count that is nearest to the best
-    // time, at its worst, over prompts and spread rows, in chunks of at least a
-    // key tile and in shorter ones.  1132 random launches of ten head layouts,
-    // against the fastest count: 3.3 % slower on average (7.6 by the number of
-    // rows), 4.7 % with the keys unknown.
+    // 566 in 2).  Where that is not known, the count that does best on average
+    // over a prompt and spread rows, in chunks of at least a key tile and in
+    // shorter ones, each against its own fastest.  1132 random launches of ten
+    // head layouts, against the fastest count: 3.3 % slower on average (7.6 by the
+    // number of rows), 4.8 % with the keys unknown.
     struct Form {
       double seen;
       int chunk_tokens, n_table;
     };
     const int n_cand = keys > 0 ? 1 : 4;
     const Form known = {std::min(1.0, (double)keys / ((double)m * (max_pos + 1.0))), chunk_tokens, n_table};
-    const Form forms[4] = {keys > 0 ? known : Form{1.0, KT, 1}, {0.5, KT, 1}, {1.0, 16, 1}, {0.5, 16, 1}};
+    const double prompt = std::max(0.5, 1 - 0.5 * m / (max_pos + 1.0));
+    const Form forms[4] = {keys > 0 ? known : Form{prompt, KT, 1}, {0.5, KT, 1}, {prompt, 16, 1}, {0.5, 16, 1}};
     double us[4][kMaxSplits], least[4];
     for (int f = 0; f < n_cand; ++f) {
       least[f] = 1e30;
@@ -1274,10 +1275,10 @@ int attention_auto_splits(int m, int max_pos, int64_t keys, int n_q, int n_kv, i
     }
     double best = 1e30;
     for (int c = 1; c <= cap; ++c) {
-      double worst = 0;
-      for (int f = 0; f < n_cand; ++f) worst = std::max(worst, us[f][c - 1] / least[f]);
-      if (worst < best) {
-        best = worst;
+      double sum = 0;
+      for (int f = 0; f < n_cand; ++f) sum += us[f][c - 1] / least[f];
+      if (sum < best) {
+        best = sum;
         ns = c;
       }
     }
