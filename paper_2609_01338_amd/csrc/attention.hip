@@ -1110,10 +1110,11 @@ template <int HD, int NW, bool SPLIT>
 void launch_nw(const _Float16* Q, const int32_t* qpos, int m, const uint8_t* S, const int32_t* table,
                int C, int cshift, int64_t slot_bytes, int nq, int nkv, int group, int qw, int gpw, int n_table,
                float scale_log2, _Float16* O, const SplitArgs& sa, int* wq, hipStream_t s) {
-  if (C >= KT)
+  // (four waves take heads of 128 from chunks of at least a key tile only: attn_four_waves)
+  if (C >= KT || (HD == 128 && NW == 4))
     launch_nwd<HD, NW, true, SPLIT>(Q, qpos, m, S, table, C, cshift, slot_bytes, nq, nkv, group, qw, gpw, n_table,
                                     scale_log2, O, sa, wq, s);
-  else
+  else if constexpr (HD != 128 || NW != 4)
     launch_nwd<HD, NW, false, SPLIT>(Q, qpos, m, S, table, C, cshift, slot_bytes, nq, nkv, group, qw, gpw, n_table,
                                      scale_log2, O, sa, wq, s);
 }
