@@ -505,13 +505,15 @@ mz_status mz_q4_gemm_split_noalloc(const void *x_f16, int32_t m, int32_t n_pad, 
 int32_t mz_q4_gemm_auto_splits(int32_t m, int32_t n_pad, int32_t k, int64_t workspace_bytes);
 
 /* The launches that mz_q4_gemm (workspace_bytes 0) or mz_q4_gemm_ex with
- * workspace_bytes of workspace makes of a product: for each of them four
+ * workspace_bytes of workspace makes of a product, with work queues (nonzero;
+ * epilogues 0-2) or without: for each of them four
  * values in plan_out (room for 8), the rows it takes, the rows and columns of
  * its tiles and its K splits (1: none).  Returns how many launches there are,
  * 1 or 2 (the second takes the rows after the last whole 256-row tile), or 0
  * for invalid sizes.  Weights that do not start on a 16-byte boundary run as
  * 256 x 256 tiles instead.  Host only, no GPU work. */
-int32_t mz_q4_gemm_plan(int32_t m, int32_t n_pad, int32_t k, int64_t workspace_bytes, int32_t *plan_out);
+int32_t mz_q4_gemm_plan(int32_t m, int32_t n_pad, int32_t k, int64_t workspace_bytes, int32_t work_queues,
+                        int32_t *plan_out);
 
 /* The K splits with which a product whose 256-row tiles are too few for the
  * GPU, while its 64-row tiles would fill it, makes about one round of the

@@ -1009,7 +1009,12 @@ int gemm_splits(int k, int n_split) {
 // elsewhere smaller tiles fill the chip (1.5B down projection, 4979 rows, 120
 // tiles of 256 rows: 213 us before as 64-row tiles of 256 columns, 137 now as
 // 128 x 128), and two workgroups per CU hide each other's start and end (1.5B
-// gate/up, 4979 rows: 255 us as 128 x 256, 284 as 256 x 256).
+// gate/up, 4979 rows: 255 us as 128 x 256, 284 as 256 x 256).  Launches that
+// take the work queues have no ragged last round and no slowest XCD at their
+// end (kQueueTime): the 8B gate/up of 32896 rows, back to back with itself 6506
+// us against 6348 as 128 x 256, takes in a restore 6.23 ms against 6.31, and
+// the down product that follows it 3.12 against 3.25 (TTFT 609.4 against 616.6
+// ms; a 4-layer model of 10340 rows 15.6 against 15.9, of 24832 43.3 and 43.6).
 struct GemmPlan {
   int rows = 0, row_tile = 256, col_tile = 256, n_split = 1;
   double us = 1e30;
@@ -1026,16 +1031,19 @@ constexpr TileTimes kTiles[] = {{256, 256, 1.40, 1.64, 4}, {128, 256, 1.10, 1.70
                                 {64, 128, 0.40, 0.68, 1},  {32, 128, 0.34, 0.56, 1}};
 
 // kSecondUs: the second workgroup of a CU starts behind the first
-constexpr double kLaunchUs = 3.0, kSecondUs = 1.0, kReduceUs = 3.2, kBytesPerUs = 5e6;
+// kQueueTime: of the static form's time, through the work queues
+constexpr double kLaunchUs = 3.0, kSecondUs = 1.0, kReduceUs = 3.2, kBytesPerUs = 5e6, kQueueTime = 0.96;
 constexpr int kMinSplitSteps = 4;
 
-double plan_us(int m, int n, int k, const TileTimes& t, int ns) {
+// queued: whole 256-row tiles may take the work queues
+double plan_us(int m, int n, int k, const TileTimes& t, int ns, bool queued = false) {
   const double cus = device_cus();
   const double w = (double)(n / t.col_tile) * ((m + t.row_tile - 1) / t.row_tile) * ns;
   const double round = t.row_tile == 256 ? cus : 2 * cus;
   const double full = std::floor(w / round), rem = w - full * round;
   double steps = full * t.t_hi;
   if (rem > 0) steps += rem <= round / 2 ? t.t_lo : t.t_lo + (t.t_hi - t.t_lo) * (rem - round / 2) / (round / 2);
+  if (queued && t.row_tile == 256 && ns == 1 && w >= kQueueMinRounds * cus) steps = w / round * t.t_hi * kQueueTime;
   const double out = (double)ns * m * n * 4 / kBytesPerUs;
   const double second = t.row_tile < 256 && w > cus ? kSecondUs : 0.;
   return kLaunchUs + second + (gemm_k_steps(k, ns) + t.extra - 1) * steps + out + (ns > 1 ? kReduceUs + out : 0.);
@@ -1055,7 +1063,7 @@ GemmPlan gemm_plan_asked(int m, int n, int k, int n_split, bool rows_ok) {
 
 // The plan of a product of m rows with at most max_split splits whose
 // partials fit ws_cap bytes.  rows_ok: the tiles of gemm_rows.hip may run.
-GemmPlan gemm_plan(int m, int n, int k, int64_t ws_cap, int max_split, bool rows_ok) {
+GemmPlan gemm_plan(int m, int n, int k, int64_t ws_cap, int max_split, bool rows_ok, bool queued = false) {
   static const int kSplits[] = {1, 2, 3, 4, 6, 8, 12, 16, 24, 32};
   GemmPlan best;
   const int nk = k / BK;
@@ -1069,7 +1077,7 @@ GemmPlan gemm_plan(int m, int n, int k, int64_t ws_cap, int max_split, bool rows
       if (want > max_split || (want > 1 && (many || nk / want < kMinSplitSteps))) break;
       const int ns = gemm_splits(k, want);
       if (ns > 1 && gemm_splitk_ws_bytes(m, n, ns) > ws_cap) break;
-      const double us = plan_us(m, n, k, t, ns);
+      const double us = plan_us(m, n, k, t, ns, queued);
       if (us < best.us) best = GemmPlan{m, t.row_tile, t.col_tile, ns, us};
     }
   }
@@ -1155,12 +1163,12 @@ void launch_planned(const GemmPlan& plan, const _Float16* X, const int32_t* a_ro
 // ragged last row of 256-row tiles can make a final round of workgroups that
 // occupies few CUs (16 column tiles x 129 row tiles = 8 rounds + 16
 // workgroups on 256 CUs).  Returns how many of p are used.
-int gemm_parts(int m, int n, int k, int64_t ws_bytes, int max_split, bool rows_ok, GemmPlan (&p)[2]) {
-  p[0] = gemm_plan(m, n, k, ws_bytes, max_split, rows_ok);
+int gemm_parts(int m, int n, int k, int64_t ws_bytes, int max_split, bool rows_ok, bool queued, GemmPlan (&p)[2]) {
+  p[0] = gemm_plan(m, n, k, ws_bytes, max_split, rows_ok, queued);
   const int full = m / BM * BM, rem = m - full;
   if (rem == 0 || full == 0) return 1;
   const GemmPlan tail = gemm_plan(rem, n, k, ws_bytes, max_split, rows_ok);
-  const double us = plan_us(full, n, k, kTiles[0], 1);
+  const double us = plan_us(full, n, k, kTiles[0], 1, queued);
   if (!(us + tail.us < p[0].us)) return 1;
   p[0] = GemmPlan{full, 256, 256, 1, us};
   p[1] = tail;
@@ -1172,7 +1180,8 @@ void launch_epi(const _Float16* X, const int32_t* a_rows, int m, int n, int k, c
                 hipStream_t s, const GemmRope& ea = GemmRope{}, int* wq = nullptr, void* ws = nullptr,
                 int64_t ws_bytes = 0, int max_split = 32) {
   GemmPlan p[2];
-  const int np = gemm_parts(m, n, k, ws_bytes, ws ? max_split : 1, gemm_rows_ok(W), p);
+  const bool queued = wq && (EPI == kEpiStore || EPI == kEpiAdd || EPI == kEpiSwiGLU);
+  const int np = gemm_parts(m, n, k, ws_bytes, ws ? max_split : 1, gemm_rows_ok(W), queued, p);
   launch_planned<EPI>(p[0], X, a_rows, 0, n, k, W, y, s, ea, wq, ws);
   if (np > 1) launch_planned<EPI>(p[1], X, a_rows, p[0].rows, n, k, W, y, s, ea, nullptr, ws);
 }
@@ -1181,9 +1190,9 @@ void launch_epi(const _Float16* X, const int32_t* a_rows, int m, int n, int k, c
 
 int64_t gemm_splitk_ws_bytes(int m, int n, int n_split) { return (int64_t)n_split * m * n * 4; }
 
-int gemm_pieces(int m, int n, int k, int64_t ws_bytes, GemmPiece (&out)[2]) {
+int gemm_pieces(int m, int n, int k, int64_t ws_bytes, bool queued, GemmPiece (&out)[2]) {
   GemmPlan p[2];
-  const int np = gemm_parts(m, n, k, ws_bytes, ws_bytes > 0 ? 32 : 1, true, p);
+  const int np = gemm_parts(m, n, k, ws_bytes, ws_bytes > 0 ? 32 : 1, true, queued, p);
   for (int i = 0; i < np; ++i) out[i] = GemmPiece{p[i].rows, p[i].row_tile, p[i].col_tile, p[i].n_split};
   return np;
 }

@@ -61,12 +61,12 @@ void launch_gemm_q4_rope(const void* x, int m, int n, int k, const void* w, int 
                          void* ws = nullptr, int64_t ws_bytes = 0);
 
 // The launches that launch_gemm_q4 makes of m rows with ws_bytes of workspace
-// (0: none) and weights on a 16-byte boundary: rows, tile and K splits of
-// each; returns how many (1 or 2).
+// (0: none), with or without work queues, and weights on a 16-byte boundary:
+// rows, tile and K splits of each; returns how many (1 or 2).
 struct GemmPiece {
   int rows, row_tile, col_tile, n_split;
 };
-int gemm_pieces(int m, int n, int k, int64_t ws_bytes, GemmPiece (&out)[2]);
+int gemm_pieces(int m, int n, int k, int64_t ws_bytes, bool queued, GemmPiece (&out)[2]);
 
 // Split-K form for few rows: gemm_splits(k, n_split) ranges of whole 64-wide
 // K steps, as many of n_split equal ones as are not empty, write fp32 partials

@@ -1949,12 +1949,13 @@ int32_t mz_q4_gemm_auto_splits(int32_t m, int32_t n_pad, int32_t k, int64_t work
   return mzk::gemm_auto_splits(m, n_pad, k, workspace_bytes);
 }
 
-int32_t mz_q4_gemm_plan(int32_t m, int32_t n_pad, int32_t k, int64_t workspace_bytes, int32_t* plan_out) {
+int32_t mz_q4_gemm_plan(int32_t m, int32_t n_pad, int32_t k, int64_t workspace_bytes, int32_t work_queues,
+                        int32_t* plan_out) {
   if (!plan_out || m < 1 || n_pad < mzk::kGemmTileN || n_pad % mzk::kGemmTileN || k < mzk::kGemmTileK ||
       k % mzk::kGemmTileK || workspace_bytes < 0)
     return 0;
   mzk::GemmPiece p[2];
-  const int np = mzk::gemm_pieces(m, n_pad, k, workspace_bytes, p);
+  const int np = mzk::gemm_pieces(m, n_pad, k, workspace_bytes, work_queues != 0, p);
   for (int i = 0; i < np; ++i) {
     const int32_t v[4] = {p[i].rows, p[i].row_tile, p[i].col_tile, p[i].n_split};
     std::copy(v, v + 4, plan_out + 4 * i);

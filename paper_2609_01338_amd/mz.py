@@ -125,7 +125,7 @@ def lib() -> ctypes.CDLL:
         "mz_q4_gemm_split_workspace_bytes": ([i32, i32, i32], i64),
         "mz_q4_gemm_split_noalloc": ([vp, i32, i32, i32, vp, i32, vp, i32, vp], i32),
         "mz_q4_gemm_auto_splits": ([i32, i32, i32, i64], i32),
-        "mz_q4_gemm_plan": ([i32, i32, i32, i64, vp], i32),
+        "mz_q4_gemm_plan": ([i32, i32, i32, i64, i32, vp], i32),
         "mz_q4_gemm_long_k_splits": ([i32, i32, i32, i64], i32),
         "mz_attention_split": ([vp, vp, i32, i32, vp, vp, i32, i32, i32, i32, i32, i32, vp, i64, vp, vp], i32),
         "mz_attention_split_workspace_bytes": ([i32, i32, i32, i32], i64),
@@ -408,10 +408,10 @@ def mz_q4_gemm_auto_splits(m: int, n_pad: int, k: int, ws_bytes: int) -> int:
     return int(lib().mz_q4_gemm_auto_splits(m, n_pad, k, ws_bytes))
 
 
-def mz_q4_gemm_plan(m: int, n_pad: int, k: int, ws_bytes: int = 0) -> list:
+def mz_q4_gemm_plan(m: int, n_pad: int, k: int, ws_bytes: int = 0, queued: bool = False) -> list:
     """(rows, row tile, column tile, K splits) of each launch of the product."""
     out = (ctypes.c_int32 * 8)()
-    n = int(lib().mz_q4_gemm_plan(m, n_pad, k, ws_bytes, out))
+    n = int(lib().mz_q4_gemm_plan(m, n_pad, k, ws_bytes, int(queued), out))
     return [tuple(out[4 * i:4 * i + 4]) for i in range(n)]
 
 

@@ -234,6 +234,9 @@ def test_gemm_plan():
     assert mz.mz_q4_gemm_plan(4096, 16384, 192) == [(4096, 128, 256, 1)]
     assert mz.mz_q4_gemm_plan(4096, 16384, 5440) == [(4096, 256, 256, 1)]
     assert mz.mz_q4_gemm_plan(16400, 16384, 6016) == [(16384, 256, 256, 1), (16, 32, 128, 1)]
+    # the largest products, with the work queues the restore passes, take 256 x 256 tiles and the queues
+    assert mz.mz_q4_gemm_plan(32896, 28672, 4096, ws, True)[0] == (32768, 256, 256, 1)
+    assert mz.mz_q4_gemm_plan(32896, 28672, 4096, ws) == [(32896, 128, 256, 1)]
     assert mz.mz_q4_gemm_plan(1000, 4096, 14336, ws) == [(1000, 128, 256, 4)]
     assert mz.mz_q4_gemm_plan(2000, 4096, 14336, ws) == [(2000, 256, 256, 2)]
     assert mz.mz_q4_gemm_plan(2000, 4096, 14336)[0][3] == 1
@@ -241,7 +244,7 @@ def test_gemm_plan():
     for _ in range(2000):
         m, n = int(2 ** rng.uniform(0, 15)), 256 * int(2 ** rng.uniform(0, 7))
         k, wsb = 64 * int(2 ** rng.uniform(0, 8)), int(rng.choice([0, 1 << 20, ws]))
-        p = mz.mz_q4_gemm_plan(m, n, k, wsb)
+        p = mz.mz_q4_gemm_plan(m, n, k, wsb, bool(rng.integers(2)))
         assert sum(r[0] for r in p) == m and 1 <= len(p) <= 2, (m, n, k, wsb, p)
         if len(p) == 2:
             assert p[0][0] % 256 == 0 and p[0][1:] == (256, 256, 1), (m, n, k, wsb, p)

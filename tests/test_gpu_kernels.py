@@ -655,7 +655,7 @@ def test_gemm_queued(M, N, K, epi):
     the queues stay untouched, one workgroup per tile (test_gemm_queues_taken
     has the products that take them).  Against the exact product on sampled
     rows and bit-equal to mz_q4_gemm."""
-    assert all(p[1:3] != (256, 256) for p in mz.mz_q4_gemm_plan(M, 2 * N if epi == 2 else N, K))
+    assert all(p[1:3] != (256, 256) for p in mz.mz_q4_gemm_plan(M, 2 * N if epi == 2 else N, K, 0, True))
     rows = None
     if M > 4000:
         rng = np.random.default_rng(M)
@@ -675,7 +675,7 @@ def test_gemm_queues_taken(M, epi):
     zero, twice."""
     torch = torch_cuda()
     N, K = 16384, 6016
-    plan = mz.mz_q4_gemm_plan(M, N, K)
+    plan = mz.mz_q4_gemm_plan(M, N, K, 0, True)
     assert plan[0] == (16384, 256, 256, 1) and 16384 // 256 * (N // 256) >= 4096, plan
     gen = torch.Generator(device="cuda").manual_seed(M + epi)
     X = torch.randn(M, K, device="cuda", generator=gen).half()
