@@ -1027,12 +1027,20 @@ struct TileTimes {
   int row_tile, col_tile;
   double t_lo, t_hi, extra;
 };
-constexpr TileTimes kTiles[] = {{256, 256, 1.40, 1.64, 4}, {128, 256, 1.10, 1.70, 1}, {128, 128, 0.56, 0.97, 1},
+constexpr TileTimes kTiles[] = {{256, 256, 1.40, 1.64, 4}, {128, 256, 1.10, 1.70, 1}, {128, 128, 0.60, 0.97, 1},
                                 {64, 128, 0.40, 0.68, 1},  {32, 128, 0.34, 0.56, 1}};
 
-// kSecondUs: the second workgroup of a CU starts behind the first
+// kSecondStep: the first CU that takes a second one sets the end of the launch,
+// so the step time goes up there by this share of the way to t_hi at once (3B
+// down projection of 1294 rows: 264 tiles of 128 x 128 112 us, 504 of 64 x 128
+// 85).  1288 products of 16 to 16384 rows, timed in every tile form and split
+// count: the pick is 1.4 % slower than the fastest form on average (2.0
+// without the rule and with 0.56 for 128 x 128 tiles, which took
+// the 1B down projection's 256 tiles for faster than they are: 1.37 ms a
+// restore against 1.27 in two splits).
+constexpr double kSecondStep = 0.6;
 // kQueueTime: of the static form's time, through the work queues
-constexpr double kLaunchUs = 3.0, kSecondUs = 1.0, kReduceUs = 3.2, kBytesPerUs = 5e6, kQueueTime = 0.96;
+constexpr double kLaunchUs = 3.0, kReduceUs = 3.2, kBytesPerUs = 5e6, kQueueTime = 0.96;
 constexpr int kMinSplitSteps = 4;
 
 // queued: whole 256-row tiles may take the work queues
@@ -1042,11 +1050,14 @@ double plan_us(int m, int n, int k, const TileTimes& t, int ns, bool queued = fa
   const double round = t.row_tile == 256 ? cus : 2 * cus;
   const double full = std::floor(w / round), rem = w - full * round;
   double steps = full * t.t_hi;
-  if (rem > 0) steps += rem <= round / 2 ? t.t_lo : t.t_lo + (t.t_hi - t.t_lo) * (rem - round / 2) / (round / 2);
+  if (rem > 0 && rem <= round / 2) steps += t.t_lo;
+  if (rem > round / 2) {
+    const double jump = t.row_tile == 256 ? 0. : kSecondStep;
+    steps += t.t_lo + (t.t_hi - t.t_lo) * (jump + (1 - jump) * (rem - round / 2) / (round / 2));
+  }
   if (queued && t.row_tile == 256 && ns == 1 && w >= kQueueMinRounds * cus) steps = w / round * t.t_hi * kQueueTime;
   const double out = (double)ns * m * n * 4 / kBytesPerUs;
-  const double second = t.row_tile < 256 && w > cus ? kSecondUs : 0.;
-  return kLaunchUs + second + (gemm_k_steps(k, ns) + t.extra - 1) * steps + out + (ns > 1 ? kReduceUs + out : 0.);
+  return kLaunchUs + (gemm_k_steps(k, ns) + t.extra - 1) * steps + out + (ns > 1 ? kReduceUs + out : 0.);
 }
 
 // The plan of a product of m rows in exactly n_split ranges of K.

@@ -240,6 +240,8 @@ def test_gemm_plan():
     assert mz.mz_q4_gemm_plan(1000, 4096, 14336, ws) == [(1000, 128, 256, 4)]
     assert mz.mz_q4_gemm_plan(2000, 4096, 14336, ws) == [(2000, 256, 256, 2)]
     assert mz.mz_q4_gemm_plan(2000, 4096, 14336)[0][3] == 1
+    # 264 tiles of 128 x 128 would put a second one on 8 CUs, which all the others wait for
+    assert mz.mz_q4_gemm_plan(1294, 3072, 8192) == [(1294, 64, 128, 1)]
     rng = np.random.default_rng(4)
     for _ in range(2000):
         m, n = int(2 ** rng.uniform(0, 15)), 256 * int(2 ** rng.uniform(0, 7))

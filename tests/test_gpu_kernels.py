@@ -133,16 +133,16 @@ def test_gemm_split(M, N, K, epi):
                                        (2048, 1024, 8192, 2)])
 def test_gemm_long_k_split(M, N, K, epi):
     """Products with too few 256-row tiles for the chip but a long K range,
-    as the restore launches them (with its workspace): they run as 128 x 128
-    tiles over all of K (test_gemm_planned_splits has those that split).  The
-    1B down projection, a ragged last row tile, half the K range, and the
-    SwiGLU epilogue, against the exact product on one row in every 64-row
-    tile."""
-    assert [p[1:] for p in mz.mz_q4_gemm_plan(M, 2 * N if epi == 2 else N, K, 64 << 20)] == [(128, 128, 1)]
+    as the restore launches them (with its workspace): 128 x 128 tiles in two
+    splits, of half the K range in one.  The 1B down projection, a ragged last
+    row tile, half the K range, and the SwiGLU epilogue, against the exact
+    product on one row in every 64-row tile."""
+    plan = [p[1:] for p in mz.mz_q4_gemm_plan(M, 2 * N if epi == 2 else N, K, 64 << 20)]
+    assert plan == [(128, 128, 2 if K == 8192 else 1)]
     _gemm_case(M, N, K, epi, seed=M + N + K + 5, sample_rows=_tile_rows(M, 64, M + K), n_split="long-k")
 
 
-@pytest.mark.parametrize("M,plan", [(17, (32, 128, 8)), (40, (64, 128, 8)), (128, (128, 128, 8)), (1000, (128, 256, 4)),
+@pytest.mark.parametrize("M,plan", [(17, (32, 128, 16)), (40, (64, 128, 8)), (128, (128, 128, 8)), (1000, (128, 256, 4)),
                                     (1900, (128, 256, 2)), (1921, (256, 256, 2)), (2048, (256, 256, 2))])
 def test_gemm_planned_splits(M, plan):
     """The 8B down projection as the restore launches it (64 MiB of workspace,
@@ -407,7 +407,7 @@ def test_gemm_tile_shapes_same_bits(epi, hd, K):
         return slab.view(-1, 2, slot // 4) if epi == 5 else y
 
     assert mz.mz_q4_gemm_plan(M, N, K) == [(M, 128 if K == 192 else 256, 256, 1)]
-    small = {mz.mz_q4_gemm_plan(m, N, K)[0][1:3] for m in (1, 65, 300)}
+    small = {mz.mz_q4_gemm_plan(m, N, K)[0][1:3] for m in (1, 65, 129)}
     assert small == {(32, 128), (64, 128), (128, 128)}
     full = run(M)
     assert bool((full != 0).any())
