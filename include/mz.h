@@ -543,8 +543,10 @@ mz_status mz_attention(const void *q_f16, const int32_t *qpos, int32_t m, const 
  * more of the work.  work_queues: device, caller-owned, 16 int32 that are
  * zero before the first call; each call leaves them zero.  Calls that share
  * them must not be in flight at the same time.  Where n_kv_heads does not
- * divide 8 or chunk_tokens < 64 this runs as mz_attention.  EINVAL as
- * mz_attention, and for a NULL work_queues. */
+ * divide 8 or chunk_tokens < 64, and with fewer than 8 query heads per KV head
+ * up to 98304 (row, query head) pairs (one and a half rounds of workgroups on
+ * 256 compute units, which even out without), this runs as mz_attention.
+ * EINVAL as mz_attention, and for a NULL work_queues. */
 mz_status mz_attention_queued(const void *q_f16, const int32_t *qpos, int32_t m, const void *slab,
                               const int32_t *table, int32_t n_table, int32_t chunk_tokens,
                               int32_t n_q_heads, int32_t n_kv_heads, int32_t head_dim, void *out_f16,

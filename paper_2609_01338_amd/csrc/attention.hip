@@ -563,7 +563,7 @@ __device__ __forceinline__ int attn_pop(int* wq, int home, int nkv, int n_items)
 // a tile in a row.
 //
 // Persistent form (wq != nullptr, nkv divides 8, chunks of at least 64
-// tokens, no key split; one workgroup per resident slot): each workgroup pops items from the queue of its XCD's KV head
+// tokens, no key split, eight waves; one workgroup per resident slot): each workgroup pops items from the queue of its XCD's KV head
 // (hardware XCC id % nkv), heaviest first, so the same L2 sharing holds; an
 // XCD whose queue runs dry takes the lightest tiles left in the others.  The
 // XCDs run at different clocks under the power limit, and with a fixed share
@@ -578,8 +578,8 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_kernel(const _Float16* __rest
                                                        float scale_log2, _Float16* __restrict__ O, int tps,
                                                        _Float16* __restrict__ Opart,
                                                        float2* __restrict__ MLpart, int* __restrict__ wq) {
-  // only the direct-load, unsplit instances have the persistent form
-  constexpr bool kCanPersist = DIRECT && !SPLIT;
+  // only the direct-load, unsplit instances of eight waves have the persistent form
+  constexpr bool kCanPersist = DIRECT && !SPLIT && NW == 8;
   if constexpr (!kCanPersist) {
     const int b = blockIdx.x;
     const int xcd = b % 8, j = b / 8;
@@ -1093,7 +1093,7 @@ void launch_nwd(const _Float16* Q, const int32_t* qpos, int m, const uint8_t* S,
   // items per KV head: query tiles times the head subsets of its group
   const int n_items = (m + bq - 1) / bq * (group / gpw);
   int blocks;
-  if (DIRECT && !SPLIT && wq && 8 % nkv == 0) {
+  if (DIRECT && !SPLIT && NW == 8 && wq && 8 % nkv == 0) {
     // persistent: one workgroup per resident slot, at most one per item
     blocks = (int)std::min<int64_t>((int64_t)n_items * nkv, resident_wgs<HD, NW, DIRECT, SPLIT>(lds_bytes));
   } else {
@@ -1138,6 +1138,11 @@ void launch_any(const void* q, const int32_t* qpos, int m, const void* slab, con
   if (attn_four_waves(m, n_q, group, head_dim, chunk_tokens, n_table, split, sa.n_split)) {
     gpw = attn_four_heads(group);
     qw = 4 / gpw;
+    // the static order pairs heavy and light items on a CU, which the order of
+    // the pops does not (2048 causal rows, us, static and through the queues:
+    // 32/8 heads of 128 54.6 and 90.8, of 64 34.4 and 75.6, 12/2 of 128 41.5 and
+    // 43.6; eight waves through the queues 69.3, 54.8, 56.7)
+    wq = nullptr;
   }
   const float scale_log2 = 1.4426950408889634f / __builtin_sqrtf((float)head_dim);
   const _Float16* Q = reinterpret_cast<const _Float16*>(q);

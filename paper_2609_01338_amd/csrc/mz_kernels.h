@@ -117,8 +117,9 @@ int gemm_long_k_splits(int m, int n, int k, int64_t ws_cap);
 // n_table entries (at most kAttnTableMax).  With
 // work_queues (device, kAttnQueueInts int32, zero on entry and left zero on
 // return; not shared by launches in flight together) and n_kv dividing 8,
-// persistent workgroups take the query tiles from per-KV-head queues, so
-// XCDs that run faster take more of them; otherwise one workgroup per tile.
+// persistent workgroups of launches of more than one and a half rounds take the
+// query tiles from per-KV-head queues, so XCDs that run faster take more of
+// them; otherwise one workgroup per tile.
 constexpr int kAttnQueueInts = 16;
 constexpr int kAttnTableMax = 8192;
 void launch_attention(const void* q, const int32_t* qpos, int m, const void* slab,

@@ -832,14 +832,31 @@ def test_attention_full_context_gappy_1p5b():
     (32, 8, 128, 256, 3000), (24, 8, 128, 256, 1700), (12, 2, 128, 256, 1030), (16, 4, 64, 64, 900),
     (8, 8, 128, 64, 200), (6, 1, 64, 128, 700), (12, 3, 64, 256, 600), (4, 4, 128, 8, 77)])
 def test_attention_queued(nq, nkv, hd, C, S):
-    """The work-queue form: 1, 2, 4 and 8 KV heads (queues shared by 8, 4, 2
-    and 1 XCDs), more tiles than workgroups and fewer, gappy query rows; 3
-    KV heads and 8-token chunks take the one-tile-per-workgroup form."""
+    """mz_attention_queued with 1, 2, 4 and 8 KV heads, gappy query rows and a
+    single one, up to one and a half rounds of workgroups: those take the
+    one-tile-per-workgroup form, as 3 KV heads and 8-token chunks always do
+    (test_attention_queues_taken has the launches that take the queues)."""
     rng = np.random.default_rng(S + 1)
     gappy = np.sort(rng.choice(S, max(1, S // 3), replace=False))
     _attn_case(nq, nkv, hd, C, S, np.arange(S), seed=11, n_split="queued")
     _attn_case(nq, nkv, hd, C, S, gappy, seed=12, n_split="queued")
     _attn_case(nq, nkv, hd, C, S, [S - 1], seed=13, n_split="queued")
+
+
+@pytest.mark.parametrize("nq,nkv,hd,C,m", [(32, 8, 128, 64, 3073), (16, 4, 64, 128, 6200), (12, 2, 128, 256, 8200),
+                                           (7, 1, 64, 64, 14100), (8, 1, 128, 256, 700), (16, 2, 64, 64, 12000)])
+def test_attention_queues_taken(nq, nkv, hd, C, m):
+    """Launches that take the work queues: more than 98304 (row, head) pairs
+    with 1, 2, 4 and 8 KV heads (queues shared by 8, 4, 2 and 1 XCDs), and
+    groups of 8 heads, which take them at any size (fewer tiles than
+    workgroups among them).  Rows spread over twice as many positions, once
+    with the longest chunk table; the bits of mz_attention, queues left zero,
+    sampled rows exact."""
+    assert m * nq > 98304 or nq // nkv == 8
+    rng = np.random.default_rng(m)
+    qpos = np.sort(rng.choice(2 * m, m, replace=False)).astype(np.int32)
+    _attn_case(nq, nkv, hd, C, 2 * m, qpos, seed=m, sample=rng.choice(m, 24, replace=False), n_split="queued",
+               n_table=8192 if m == 3073 else None)
 
 
 def test_attention_max_table():
