@@ -519,7 +519,8 @@ int32_t mz_q4_gemm_plan(int32_t m, int32_t n_pad, int32_t k, int64_t workspace_b
  * GPU, while its 64-row tiles would fill it, makes about one round of the
  * compute units of 256-row tiles, when every split keeps at least 16 K steps
  * of 64 and the fp32 partials (splits x m x n_pad x 4 bytes) fit
- * workspace_bytes; 1 otherwise.  Host only, no GPU work. */
+ * workspace_bytes; 1 otherwise.  No call takes this count by itself
+ * (mz_q4_gemm_plan has what they take).  Host only, no GPU work. */
 int32_t mz_q4_gemm_long_k_splits(int32_t m, int32_t n_pad, int32_t k, int64_t workspace_bytes);
 
 /* Causal GQA attention (paper Sec. 2.1; read through the chunk table as in

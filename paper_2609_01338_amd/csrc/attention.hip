@@ -1022,7 +1022,9 @@ inline int attn_four_heads(int group) { return group % 4 == 0 ? 4 : group % 2 ==
 // the queries, which costs 26 % where the chip is full of items; but a launch
 // of few items lasts as long as its heaviest, and two half-size ones on a CU
 // even out: up to one and a half rounds of the CUs (an item is 256 (row, head)
-// pairs), and every key split.  Same bits.  On one MI355X, us, eight against
+// pairs; not through the work queues, see launch_any), and every key split,
+// where they are the faster form in most sizes but not in all (128 rows at 32768
+// keys in 16 splits, whole rounds of either: 84-86 us, with eight 82).  Same bits.  On one MI355X, us, eight against
 // four waves: 2048 causal rows, 32/8 heads of 64 (256 items) 41.0 and 34.9;
 // 2048 rows, 12/2 heads of 128 (96 items) 55.3 and 41.3; 3072 rows, 32/8 of
 // 128 (384) 94.3 and 92.4, 4096 (512) 146.6 and 149.6; 17 rows at 32768 keys
@@ -1030,7 +1032,9 @@ inline int attn_four_heads(int group) { return group % 4 == 0 ? 4 : group % 2 ==
 // rows at 16384 in 4 splits 332 and 309.  Chunks shorter than a key tile come
 // through registers, which four waves have fewer of per row: with heads of 128
 // eight waves stay (17 rows, 31 splits 63 against 75), with 64 the line is at
-// half a round (1024 rows 28.0 and 27.0, 2048 49.9 and 50.6).
+// half a round (1024 rows 28.0 and 27.0, 2048 49.9 and 50.6; 2121 random split
+// launches: median 0.94-0.99 of eight waves' time up to half a round of items,
+// 1.01-1.03 for one and two rounds, 0.7 where half of their tiles is empty).
 inline bool attn_four_waves(int m, int n_q, int group, int head_dim, int chunk_tokens, int n_table, bool split,
                             int n_split) {
   if (group >= 8) return false;

@@ -14,7 +14,7 @@
 // values a group's min and max took four exchanges each, and every value a
 // correctly rounded division (23.3 us for 22.5 M halves, 14.4 now: 4.8 TB/s;
 // decompression 13.5).  Now two exchanges serve 16 values, and
-// a value is multiplied by 1 / d; only where that lands within 1e-3 of the
+// a value is multiplied by 1 / d; only where that lands within 5e-4 of the
 // middle between two codes is it divided (see quantize).
 #include "mz_kernels.h"
 
@@ -29,8 +29,8 @@ constexpr int G = 64, PER = 16, LANES = G / PER;   // values per group and per l
 // clamp(rint(RN(a / d)), 0, 255), RN the correctly rounded fp32 quotient.  t =
 // a * rd is within 1e-4 of a / d (codes up to 256, rd = 1 / d rounded), so
 // rint(t) is the code unless a / d lies that close to the middle between two
-// codes; the distance from q d to a, exact to one rounding, tells, and then the
-// quotient is formed.  (NaN compares false and ends as code 0, as the division's
+// codes; the distance from q d to a, exact to one rounding, tells (by 5e-4: 2 |e|
+// within d / 1024 of d), and then the quotient is formed.  (NaN compares false and ends as code 0, as the division's
 // does; so do the quotients of an infinite d.)
 __device__ __forceinline__ uint32_t quantize(float a, float d, float rd) {
   float q = __builtin_rintf(a * rd);

@@ -1216,9 +1216,11 @@ int gemm_auto_splits(int m, int n, int k, int64_t ws_cap) {
   const int bm = (n / BN) * ((m + 255) / 256) < 128 ? 64 : 256;
   const int tiles = (n / BN) * ((m + bm - 1) / bm);
   const int nk = k / BK;
-  // about two workgroups per CU, at least 4 K steps per split.  From 1024
-  // rows on, tiles that cover half the CUs run whole: there the partials and
-  // their reduce cost more than the idle CUs save
+  // A count from the sizes alone, by tiles of 64 or 256 rows and 256 columns:
+  // two of them per CU, at least 4 K steps per split, whole from 1024 rows on
+  // where they cover half the CUs.  A single row's split GEMV takes it as it
+  // is; with more rows it is the limit under which the plan chooses (its tiles
+  // are others).
   constexpr int kTarget = 512, kMinSteps = 4, kMaxSplits = 32, kWholeRows = 1024;
   if (tiles >= kTarget / 2 || nk < 2 * kMinSteps || (m >= kWholeRows && tiles >= kTarget / 4)) return 1;
   int ns = std::min({(kTarget + tiles - 1) / tiles, nk / kMinSteps, kMaxSplits});
@@ -1226,6 +1228,7 @@ int gemm_auto_splits(int m, int n, int k, int64_t ws_cap) {
   return ns <= 1 ? 1 : gemm_splits(k, ns);   // no empty trailing split
 }
 
+// (a host rule of the ABI; no launch takes it)
 int gemm_long_k_splits(int m, int n, int k, int64_t ws_cap) {
   constexpr int kMinSteps = 16;
   const int cus = device_cus();

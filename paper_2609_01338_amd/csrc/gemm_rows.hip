@@ -47,8 +47,8 @@ constexpr int NIB_BYTES = kGemmTileN * kGemmTileK / 2;   // code bytes of a pack
 // MI: 16-row MFMA tiles per wave; NC: 16-column groups per wave (2: 128-column
 // tiles, 4: 256).  A stage holds KT 64-wide K tiles of activations, codes and
 // scales and is consumed as two units of UK 32-wide blocks; NS stages, as many
-// as leave room for two workgroups in a CU's 160 KB (NS * STAGE: 74, 80, 66
-// and 75 KB).
+// as leave room for two workgroups in a CU's 160 KB (NS * STAGE: 68 KB for 32
+// rows, 75 for 64, 63 for 128 x 128 and 75 for 128 x 256).
 template <int MI, int NC>
 struct RowsTile {
   static constexpr int BM = 16 * MI, BN = 64 * NC;

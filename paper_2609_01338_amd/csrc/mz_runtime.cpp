@@ -391,14 +391,16 @@ const char* kKindName[kKCount] = {"embed_q4", "rmsnorm", "gemm_q4_kv", "rope_kv"
                                   "rope_q", "gather_rows", "attention", "gemm_q4_o",
                                   "gemm_q4_gateup", "gemm_q4_down", "lm_head_argmax", "attention_split",
                                   "gemm_q4_qkv_one_row"};
-// HIP kernel symbol each kind launches (to line up with profiler summaries;
-// the Q and K/V projections name their unsplit RoPE-epilogue form)
+// HIP kernel symbols each kind launches, the epilogue as the first template
+// argument (to line up with profiler summaries).  Products that split over K
+// run as <3> and a gemm_splitk_reduce (_rope for Q and K/V), single rows as
+// gemv1_kernel.
 const char* kKindKernel[kKCount] = {"embed_kernel", "rmsnorm_kernel", "gemm_q4_kernel<5>|gemm_rows_kernel<5>",
                                     "rope_kv_kernel", "gemm_q4_kernel<4>|gemm_rows_kernel<4>", "rope_kv_kernel",
                                     "gather_rows_kernel", "attn_kernel", "gemm_q4_kernel<1>|gemm_rows_kernel<1>",
                                     "gemm_q4_kernel<2>|gemm_rows_kernel<2>", "gemm_q4_kernel<1>|gemm_rows_kernel<1>",
                                     "lm_head_kernel+argmax_kernel",
-                                    "attn_kernel<split>|attn_few_kernel+attn_merge_wide_kernel",
+                                    "attn_kernel<split>|attn_few_kernel+attn_merge_wide_kernel|attn_merge_rows_kernel",
                                     "gemv1_qkv_kernel"};
 
 struct KindStats {
