@@ -32,8 +32,8 @@ METRIC = "KV-recompute prefill tokens/s + TTFT ms from evicted state, 1 MI355X"
 # valid only for the kernel source they were taken on and the 8B workload.
 MEASURED_TRAFFIC = {"kernel": "attn_kernel", "workload": "8b",
                     "source": "paper_2609_01338_amd/csrc/attention.hip",
-                    "sha256": "e8f8b9d075babd7f86c63e1cafc052914096fe103c936855e21a0ce37fea0951",
-                    "bytes_per_launch": 1.652e9}
+                    "sha256": "07b405c15730fac1f8f0336a068d110a448a8b80ace554ea619d69c8434178ec",
+                    "bytes_per_launch": 1.662e9}
 PEAK_MFMA_TFLOPS = 2500.0      # MI355X dense bf16 / fp16 MFMA
 PEAK_HBM_GBPS = 8000.0
 
