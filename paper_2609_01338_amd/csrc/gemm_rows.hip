@@ -82,6 +82,78 @@ __device__ __forceinline__ void wait_vm() {
   asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(N) : "memory");
 }
 
+// The rotary epilogue of a wave: acc[i][t] holds columns col(t) + 4 g .. + 3 of
+// the tile from column n0 on, for row row0 + 16 i (see the kernel's epilogue).
+// Positions and slot offsets come first, the angles a row tile ahead of the
+// stores: behind them each read waited for the stores before it (1.5B Q of 8320
+// rows 57.1 us, 48.7 now; 1B K/V 64.4 and 56.5, 2048 rows 20.5 and 18.0).
+template <int EPI, int MI, int NC, typename Col>
+__device__ __forceinline__ void rope_rows(const f32x4 (&acc)[MI][NC], const GemmRope& ea, void* Y, int M, int row0,
+                                          int n0, int g, const Col& col) {
+  const int half = ea.hd >> 1;
+  const int rot = EPI == kEpiRopeQ ? ea.n_valid : ea.n_valid >> 1;   // rotated columns
+  int p[MI];
+  int64_t off[MI];                                       // < 0: a row that writes nothing
+#pragma unroll
+  for (int i = 0; i < MI; ++i) {
+    p[i] = ea.pos[min(row0 + 16 * i, M - 1)];
+    off[i] = EPI == kEpiRopeKV ? ea.kv_off[min(row0 + 16 * i, M - 1)] : 0;
+  }
+#pragma unroll
+  for (int i = 0; i < MI; ++i) {
+    if (row0 + 16 * i >= M) off[i] = -1;
+    if (off[i] < 0) p[i] = 0;
+  }
+  float2 cv[2][NC / 2][4];
+  auto fetch = [&](int i, float2(&v)[NC / 2][4]) {
+#pragma unroll
+    for (int t = 0; t < NC; t += 2) {
+      const int ct = n0 + col(t);
+      if (ct >= rot) continue;
+      const float2* cs = ea.rope_cs + (size_t)p[i] * half + ((ct + 4 * g) & (2 * half - 1));
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[t / 2][e] = cs[e];
+    }
+  };
+  fetch(0, cv[0]);
+#pragma unroll
+  for (int i = 0; i < MI; ++i) {
+    if (i + 1 < MI) fetch(i + 1, cv[(i + 1) & 1]);
+    if (off[i] < 0) continue;
+#pragma unroll
+    for (int t = 0; t < NC; t += 2) {
+      const int ct = n0 + col(t), c0 = ct + 4 * g;
+      if (ct < rot) {
+        _Float16* y = EPI == kEpiRopeQ ? reinterpret_cast<_Float16*>(Y) + (size_t)(row0 + 16 * i) * ea.n_valid
+                                       : reinterpret_cast<_Float16*>(ea.slab + off[i]);
+        f16x4 o1, o2;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const float2 v = cv[i & 1][t / 2][e];
+          const float2 q = rope_rotate(acc[i][t][e], acc[i][t + 1][e], v.x, v.y);
+          o1[e] = (_Float16)q.x;
+          o2[e] = (_Float16)q.y;
+        }
+        *reinterpret_cast<f16x4_out*>(y + c0) = o1;
+        *reinterpret_cast<f16x4_out*>(y + c0 + half) = o2;
+      } else if (EPI == kEpiRopeKV) {
+        // values: V^T[c][pos % C]; the 16 lanes of a row group are 16
+        // activation rows, neighbouring positions in most launches
+        const int pc = p[i] & (ea.C - 1);
+        uint8_t* vt = ea.slab + off[i] - (int64_t)pc * ea.n_valid + (int64_t)ea.C * ea.n_valid + pc * 2;
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            const int c = c0 + h * half + e;
+            if (c < ea.n_valid)
+              *reinterpret_cast<_Float16*>(vt + (int64_t)(c - rot) * ea.C * 2) = (_Float16)acc[i][t + h][e];
+          }
+      }
+    }
+  }
+}
+
 template <int EPI, int MI, int NC>
 __global__ __launch_bounds__(NT, 2) void gemm_rows_kernel(
     const _Float16* __restrict__ X, const int32_t* __restrict__ a_rows, int M, int K, const uint8_t* __restrict__ Wp,
@@ -270,17 +342,14 @@ __global__ __launch_bounds__(NT, 2) void gemm_rows_kernel(
 
   // epilogue: lane (r, g) holds columns c + 4 g .. + 3 of each 16-column
   // group for activation row r of each 16-row tile
+  if constexpr (ROPE) {
+    rope_rows<EPI>(acc, ea, Y, M, mt * T::BM + r, nt * BN, g, col);
+    return;
+  }
 #pragma unroll
   for (int i = 0; i < MI; ++i) {
     const int row = mt * T::BM + i * 16 + r;
     if (row >= M) continue;
-    [[maybe_unused]] int p = 0;
-    [[maybe_unused]] int64_t off = 0;
-    if constexpr (ROPE) {
-      p = ea.pos[row];
-      if (EPI == kEpiRopeKV) off = ea.kv_off[row];
-      if (off < 0) continue;                             // a row that writes no KV
-    }
 #pragma unroll
     for (int t = 0; t < NC; t += 2) {
       const int ct = nt * BN + col(t), c0 = ct + 4 * g;
@@ -289,36 +358,6 @@ __global__ __launch_bounds__(NT, 2) void gemm_rows_kernel(
 #pragma unroll
         for (int e = 0; e < 4; ++e) o[e] = swiglu_f16(acc[i][t][e], acc[i][t + 1][e]);
         *reinterpret_cast<f16x4_out*>(reinterpret_cast<_Float16*>(Y) + (size_t)row * (N / 2) + ct / 2 + 4 * g) = o;
-      } else if constexpr (ROPE) {
-        const int rot = EPI == kEpiRopeQ ? ea.n_valid : ea.n_valid >> 1;   // rotated columns
-        if (ct < rot) {
-          const float2* cs = ea.rope_cs + (size_t)p * half + (c0 & (2 * half - 1));
-          _Float16* y = EPI == kEpiRopeQ ? reinterpret_cast<_Float16*>(Y) + (size_t)row * ea.n_valid
-                                         : reinterpret_cast<_Float16*>(ea.slab + off);
-          f16x4 o1, o2;
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            const float2 v = cs[e];
-            const float2 q = rope_rotate(acc[i][t][e], acc[i][t + 1][e], v.x, v.y);
-            o1[e] = (_Float16)q.x;
-            o2[e] = (_Float16)q.y;
-          }
-          *reinterpret_cast<f16x4_out*>(y + c0) = o1;
-          *reinterpret_cast<f16x4_out*>(y + c0 + half) = o2;
-        } else if (EPI == kEpiRopeKV) {
-          // values: V^T[c][pos % C]; the 16 lanes of a row group are 16
-          // activation rows, neighbouring positions in most launches
-          const int pc = p & (ea.C - 1);
-          uint8_t* vt = ea.slab + off - (int64_t)pc * ea.n_valid + (int64_t)ea.C * ea.n_valid + pc * 2;
-#pragma unroll
-          for (int h = 0; h < 2; ++h)
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-              const int c = c0 + h * half + e;
-              if (c < ea.n_valid)
-                *reinterpret_cast<_Float16*>(vt + (int64_t)(c - rot) * ea.C * 2) = (_Float16)acc[i][t + h][e];
-            }
-        }
       } else {
         float* y = reinterpret_cast<float*>(Y) + ((size_t)split * M + row) * N + c0;
 #pragma unroll
